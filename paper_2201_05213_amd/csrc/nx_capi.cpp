@@ -110,6 +110,7 @@ struct Plan {
   int K = 1;       // rANS streams per lane (ROW_STREAMS: one per lane row)
   int order = 0;   // 0 raster, 1 wavefront, 2 wavefront decoded in the sheared layout
   int ph_max = 0;  // tallest lane of the batch
+  int pw_max = 0;  // widest
   int64_t ring_waves = 0, ring_rows = 0;  // sheared context rings (set by plan_ring)
   int64_t rev_words = 0;    // encoder: coding-order symbol words of all streams
   int64_t after_words = 0;  // encoder: per-step offset entries of all streams
@@ -160,6 +161,7 @@ nellox_status make_plan(int32_t n, const nellox_image* imgs, const nellox_opts* 
     P.n_px += npx;
     P.n_tiles += (int64_t)im.H * D.ntx;
     P.ph_max = std::max(P.ph_max, D.ph);
+    P.pw_max = std::max(P.pw_max, D.pw);
     const int64_t ns = image_streams(P.K, im.H, D.nlx, D.nly);
     D.stream_base = P.n_streams;
     P.n_streams += ns;
@@ -563,6 +565,7 @@ nellox_status nellox_encode(const nellox_model* mc, int32_t n, const nellox_imag
   r.rev = (uint32_t*)(w8 + W.rev);
   r.after = (int32_t*)(w8 + W.after);
   r.max_lane_px = P.max_lane_px;
+  r.wave_per_stream = rans_wave(P.n_streams, P.K == ROW_STREAMS, m->num_cu) ? 1 : 0;
   hipError_t e = launch_rans_encode(r, s);
   if (e != hipSuccess) return hip_fail(e, "rANS encoder launch");
   PackArgs pk{};
@@ -582,6 +585,8 @@ nellox_status nellox_encode(const nellox_model* mc, int32_t n, const nellox_imag
   pk.out_offsets = out_offsets;
   pk.out_cap = out_cap;
   pk.overflow = (int32_t*)(w8 + W.flags);
+  // about 10 bits a symbol: longer streams take more rounds of the copy
+  pk.max_stream_bytes = 4 * (P.K == ROW_STREAMS ? (int64_t)P.pw_max : P.max_lane_px / P.K);
   if (n > 0) {
     e = launch_pack(pk, s);
     if (e != hipSuccess) return hip_fail(e, "container packing launch");

@@ -210,13 +210,15 @@ __global__ void __launch_bounds__(NWAVES * 64) k_pass(PassArgs A) {
 }
 
 // ------------------------------------------------------------------ rANS encoder
-// Three kernels. A stream's states are one serial chain, run by one thread,
-// and with a few thousand streams a wave has a SIMD to itself: its time per
-// symbol is its own instruction count. So the walk over the stream's
-// symbols in reverse decode order, and their loads, come out of that chain:
-// k_rans_counts and k_rans_scatter lay every stream's symbols out
-// contiguously in coding order, reading the symbol buffer in pixel order;
-// k_rans_enc then reads them in order and codes.
+// A stream's state is one serial chain, so what bounds the coder is the
+// instructions of that chain, run by a wave that has its SIMD to itself (6 to
+// 8 cycles each). Everything that does not depend on the state comes out of
+// it: k_rans_counts and k_rans_scatter lay every stream's symbols out
+// contiguously in coding order, reading the symbol buffer in pixel order, and
+// with few streams a wave codes each: its lanes prepare 64 symbols at a time,
+// the quotient by a symbol's frequency becoming a multiplication by its
+// reciprocal (k_rans_enc_wave). With many, a thread codes a stream
+// (k_rans_enc).
 
 // lane geometry of stream SL = L K + kk, and where its encoder scratch lies
 struct StreamGeom {
@@ -281,7 +283,42 @@ __global__ void __launch_bounds__(64) k_rans_counts(RansEncArgs A) {
   if (lane == 0) A.lane_len[SL] = (uint32_t)min<int64_t>(suf, G.rev_cap);
 }
 
-constexpr int SCATTER_PX = 16384;  // pixels of a lane per k_rans_scatter workgroup
+// What coding a symbol (s, f) needs besides the state: y / f is the high
+// word of y M, shifted right by sh, exactly, for every y < 2^31 (M =
+// ceil(2^(32 + sh) / f), 2^sh < f <= 2^(sh + 1), so M f exceeds the power of
+// two by e < f <= 2^(sh + 1) and y e < 2^(32 + sh)). For f = 1, M would be
+// 2^32: M = 2^32 - 1 gives y - 1, which 65535 more in the sum makes good.
+//   y -> (y / f) 2^16 + y mod f + s = y + (y / f) (2^16 - f) + s
+struct alignas(16) PutSym {
+  uint32_t M, xm;   // reciprocal; f 2^15, the state from which a byte is shed first
+  uint32_t bias;    // xm + s (f = 1: xm + s + 65535)
+  uint32_t mult;    // 2^16 - f, and sh from bit 24 up (24-bit multiplies do not see it)
+};
+NXD PutSym put_sym(uint32_t w) {
+  const uint32_t s = w & 0xffffu, f = w >> 16;
+  const uint32_t sh = 31u - (uint32_t)__builtin_clz((f - 1u) | 1u);
+  // M from a float quotient (within 2^-22 of it) corrected by its remainder:
+  // e = 2^(32 + sh) - M f modulo 2^32 is small enough to be read as signed
+  const float r = __builtin_amdgcn_rcpf((float)f);
+  uint32_t M = (uint32_t)(r * __uint_as_float((127u + 32u + sh) << 23));
+  int32_t e = -(int32_t)(M * f);
+  M += (uint32_t)(int32_t)floorf((float)e * r);
+  e = -(int32_t)(M * f);
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const bool up = e > 0, dn = e <= -(int32_t)f;
+    M += up ? 1u : dn ? 0xffffffffu : 0u;
+    e += up ? -(int32_t)f : dn ? (int32_t)f : 0;
+  }
+  PutSym P;
+  P.M = f == 1u ? 0xffffffffu : M;
+  P.xm = f << 15;
+  P.bias = P.xm + s + (f == 1u ? 65535u : 0u);
+  P.mult = ((CDF_TOTAL - f) & 0xffffffu) | (sh << 24);
+  return P;
+}
+
+constexpr int SCATTER_PX = 2048;  // pixels of a lane per k_rans_scatter workgroup
 
 // Workgroup (lane, chunk) reads a chunk of the lane's symbols in pixel order
 // (coalesced) and puts each at its place in its stream's coding order
@@ -293,26 +330,26 @@ __global__ void __launch_bounds__(256) k_rans_scatter(RansEncArgs A) {
   const int64_t L = blockIdx.x;
   const StreamGeom G = stream_geom(A, L * K);
   const int64_t npx = (int64_t)G.Hl * G.Wl;
-  const int64_t q0 = (int64_t)blockIdx.y * SCATTER_PX;
-  if (q0 >= npx) return;
-  const int64_t q1 = min<int64_t>(npx, q0 + SCATTER_PX);
-  const uint32_t* sym = A.sym + G.D.px_base * 3;
-  for (int64_t q = q0 + threadIdx.x; q < q1; q += 256) {
-    const int i = (int)(q / G.Wl), j = (int)(q - (int64_t)i * G.Wl);
-    const uint32_t* sp = sym + ((int64_t)(G.y0 + i) * G.D.W + (G.x0 + j)) * 3;
-    const uint32_t v[3] = {sp[0], sp[1], sp[2]};
+  for (int64_t q0 = (int64_t)blockIdx.y * SCATTER_PX; q0 < npx; q0 += (int64_t)gridDim.y * SCATTER_PX) {
+    const int64_t q1 = min<int64_t>(npx, q0 + SCATTER_PX);
+    const uint32_t* sym = A.sym + G.D.px_base * 3;
+    for (int64_t q = q0 + threadIdx.x; q < q1; q += 256) {
+      const int i = (int)((uint32_t)q / (uint32_t)G.Wl), j = (int)((uint32_t)q - (uint32_t)i * (uint32_t)G.Wl);
+      const uint32_t* sp = sym + ((int64_t)(G.y0 + i) * G.D.W + (G.x0 + j)) * 3;
+      const uint32_t v[3] = {sp[0], sp[1], sp[2]};
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      int kk = 0;
-      int64_t p;
-      if (A.order == 0) {
-        p = 3 * npx - 1 - (3 * q + c);
-      } else {
-        int t, off;
-        coding_slot(i, j, c, G.Hl, G.Wl, O, K, kk, t, off);
-        p = (int64_t)A.after[G.after_off + kk * G.after_cap + t] + off;
+      for (int c = 0; c < 3; ++c) {
+        int kk = 0;
+        int64_t p;
+        if (A.order == 0) {
+          p = 3 * npx - 1 - (3 * q + c);
+        } else {
+          int t, off;
+          coding_slot(i, j, c, G.Hl, G.Wl, O, K, kk, t, off);
+          p = (int64_t)A.after[G.after_off + kk * G.after_cap + t] + off;
+        }
+        if (p >= 0 && p < G.rev_cap) A.rev[G.rev_off + kk * G.rev_cap + p] = v[c];
       }
-      if (p >= 0 && p < G.rev_cap) A.rev[G.rev_off + kk * G.rev_cap + p] = v[c];
     }
   }
 }
@@ -356,87 +393,250 @@ NXD uint32_t spread_rank(uint32_t y, uint32_t s, uint32_t f) {
   return (uint32_t)n;
 }
 
-// rANS-encodes n symbols (start | freq << 16) into state x, bytes written
-// backwards at out. x / f: a float quotient (relative error below 2^-21, so
-// within one of the true one, as x / f < 2^15 after renormalisation) fixed
-// by one step of the remainder; a state below 2^31 sheds at most two bytes.
-// A state below f takes the symbol's spread slot instead.
-template <int B>
-__device__ __forceinline__ void rans_put(uint32_t& x, uint8_t*& out, const uint32_t (&v)[B], int n) {
-#pragma unroll
-  for (int k = 0; k < B; ++k) {
-    if (k < n) {
-      const uint32_t s = v[k] & 0xffffu, f = v[k] >> 16;
-      if (x < f) {  // the first pushes of a stream: a spread slot
-        x = spread_select(x, s, f);
-        continue;
-      }
-      const float rf = __builtin_amdgcn_rcpf((float)f);
-      const uint32_t xmax = ((RANS_L >> CDF_BITS) << 8) * f;
-      const uint32_t b1 = x >= xmax ? 1u : 0u;
-      const uint32_t b2 = (x >> 8) >= xmax ? 1u : 0u;
-      if (b1) out[-1] = (uint8_t)x;
-      if (b2) out[-2] = (uint8_t)(x >> 8);
-      out -= b1 + b2;
-      x >>= 8u * (b1 + b2);
-      uint32_t qt = (uint32_t)((float)x * rf);
-      int32_t r = (int32_t)(x - qt * f);
-      if (r < 0) {
-        --qt;
-        r += (int32_t)f;
-      } else if (r >= (int32_t)f) {
-        ++qt;
-        r -= (int32_t)f;
-      }
-      x = (qt << CDF_BITS) + (uint32_t)r + s;
-    }
-  }
+// A push on a state x >= f first sheds low bytes while the state is at least
+// xm = f 2^15 (two at most, the state being below 2^31): of x, x >> 8 and
+// x >> 16, the largest below xm is left. Less xm, modulo 2^32, the values
+// below xm are the large ones, in order: a maximum finds it without a
+// compare and its hazards. Returns it less xm.
+NXD uint32_t put_renorm(uint32_t x, uint32_t xm) {
+  const uint32_t a = x - xm, b = (x >> 8) - xm, c = (x >> 16) - xm;
+  return max(max(a, b), c);
+}
+// the state after pushing symbol e on x >= f
+NXD uint32_t put_state(uint32_t x, const PutSym& e) {
+  const uint32_t m = put_renorm(x, e.xm);
+  const uint32_t q = __umulhi(m + e.xm, e.M) >> (e.mult >> 24);
+  return __umul24(q, e.mult) + (m + e.bias);
 }
 
-// one thread per stream (lane L, stream k): stream index L K + k
+// The bytes a thread sheds over PUT_BATCH symbols gather in its window in LDS,
+// downwards from the window's end, and go to memory as whole words: a store
+// of each symbol's bytes is a transaction of its own at the L2, which bounded
+// the coder of the large batch (30,720 streams of 1,024 symbols on average: 195 us with
+// a store a symbol, 152 us so).
+constexpr int PUT_BATCH = 16;
+constexpr int PUT_WINDOW = 2 * PUT_BATCH;  // two bytes a symbol at most
+constexpr int PUT_STRIDE = PUT_WINDOW + 16;
+struct PutWindow {
+  uint8_t* end;  // LDS, 16-byte aligned
+  uint32_t o;    // bytes held: end - o .. end - 1
+  // to memory below `out`, the last word with up to 3 bytes below them, which
+  // the next batch overwrites (or which lie below the stream's first byte,
+  // inside its slot)
+  NXD void flush(uint8_t*& out) {
+    uint32_t w[PUT_WINDOW / 4];
+#pragma unroll
+    for (int k = 0; k < PUT_WINDOW / 16; ++k) {
+      const uint4 v = *(const uint4*)(end - 16 * (k + 1));
+      w[4 * k] = v.w;
+      w[4 * k + 1] = v.z;
+      w[4 * k + 2] = v.y;
+      w[4 * k + 3] = v.x;
+    }
+    struct __attribute__((packed)) Word {
+      uint32_t v;
+    };
+#pragma unroll
+    for (int k = 0; k < PUT_WINDOW / 4; ++k)
+      if (4u * k < o) ((Word*)(out - 4 * (k + 1)))->v = w[k];
+    out -= o;
+    o = 0;
+  }
+};
+
+// Codes symbol w (s | f << 16) into a state; the bytes it sheds go to the
+// window, the one shed first on top. Both candidates are always written: what
+// is not shed is overwritten by the symbols that follow. A state below f (the
+// first pushes of a stream) takes the symbol's spread slot and sheds nothing.
+// y / f: a float quotient made a little too small (the reciprocal times
+// 1 - 2^-21, so between the quotient less 2^-5 and the quotient, which is
+// below 2^15), and one step up if the remainder asks for it.
+NXD void put_write(uint32_t& x, uint32_t w, PutWindow& win, bool small) {
+  const uint32_t s = w & 0xffffu, f = w >> 16;
+  if (small && x < f) {
+    x = spread_select(x, s, f);
+    return;
+  }
+  const uint32_t xm = f << 15;
+  const float rf = __builtin_amdgcn_rcpf((float)f) * (1.0f - 0x1p-21f);
+  uint8_t* at = win.end - win.o;
+  at[-1] = (uint8_t)x;
+  at[-2] = (uint8_t)(x >> 8);
+  const uint32_t y = put_renorm(x, xm) + xm;
+  win.o += (x >= xm ? 1u : 0u) + ((x >> 8) >= xm ? 1u : 0u);
+  const uint32_t q = (uint32_t)((float)y * rf);
+  const uint32_t r = y - __umul24(q, f);
+  const bool up = r >= f;
+  x = ((q + (up ? 1u : 0u)) << CDF_BITS) + (r - (up ? f : 0u)) + s;
+}
+
+// the final state's significant bytes (x >= 1), most significant first
+NXD uint8_t* put_end(uint32_t x, uint8_t* out) {
+  do {
+    *--out = (uint8_t)x;
+    x >>= 8;
+  } while (x != 0u);
+  return out;
+}
+
+// One wave per stream (row streams: a lane row, its symbols read in place,
+// backwards), 64 symbols at a time: the lanes work out what the coding of a
+// symbol each needs, the first lane runs the chain (11 instructions a
+// symbol: its symbols come from LDS 8 ahead, and the states go back there),
+// and the lanes write the bytes their symbols shed, placed by counting the
+// lanes before them. Chosen while the waves of a SIMD are few (rans_wave).
+// 196,608 symbols in one stream: 36.7 ms with a chain that divided by a
+// float quotient and moved its own bytes, MEASURED_WAVE.
+template <bool ROWS>
+__global__ void __launch_bounds__(64) k_rans_enc_wave(RansEncArgs A) {
+  __shared__ PutSym ent[64 + 16];  // the last 16 are read ahead, never coded
+  __shared__ uint32_t xs[64];      // the state each symbol was pushed on
+  const int64_t SL = blockIdx.x;
+  const int lane = threadIdx.x;
+  const uint32_t* src;
+  int64_t n, slot_end, step;
+  if constexpr (ROWS) {
+    const int im = find_img_stream(A.desc, A.n_img, SL);
+    const ImgDesc D = A.desc[im];
+    const StreamAt S = stream_at(D, ROW_STREAMS, SL - D.stream_base);
+    n = 3 * (int64_t)S.Wl;
+    slot_end = S.slot_end;
+    src = A.sym + (D.px_base + (int64_t)(S.ly * D.ph + S.r) * D.W + (int64_t)S.lx * D.pw) * 3 + (n - 1);
+    step = -1;
+  } else {
+    const StreamGeom G = stream_geom(A, SL);
+    slot_end = G.D.slot_base + A.K * (6 * G.lane_px_off + 8 * (int64_t)G.q) +
+               (G.kk + 1) * lane_slot_bytes((int64_t)G.Hl * G.Wl);
+    src = A.rev + G.rev_off;
+    n = A.lane_len[SL];
+    step = 1;
+  }
+  uint8_t* out = A.slots + slot_end;  // the same in every lane
+  uint32_t x = RANS_X0;               // lane 0's is the stream's
+  uint32_t w = lane < n ? src[step * lane] : 0x10000u;
+  for (int64_t p0 = 0; p0 < n; p0 += 64) {
+    const PutSym mine = put_sym(w);
+    ent[lane] = mine;
+    const int64_t pn = p0 + 64 + lane;
+    w = pn < n ? src[step * pn] : 0x10000u;
+    const int cnt = n - p0 < 64 ? (int)(n - p0) : 64;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    if (lane == 0) {
+      int k = 0;
+      // a state from 2^23 up stays there, and above every f
+      for (; k < cnt && x < RANS_L; ++k) {
+        const PutSym e = ent[k];
+        xs[k] = x;
+        const uint32_t f = e.xm >> 15;  // where x < f, f > 1: the bias is xm + s
+        x = x < f ? spread_select(x, e.bias - e.xm, f) : put_state(x, e);
+      }
+      if (k + 8 <= cnt) {
+        PutSym ea[8], eb[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) ea[u] = ent[k + u];
+        do {
+#pragma unroll
+          for (int u = 0; u < 8; ++u) eb[u] = ent[k + 8 + u];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) {
+            xs[k + u] = x;
+            x = put_state(x, ea[u]);
+          }
+          k += 8;
+          if (k + 8 > cnt) break;
+#pragma unroll
+          for (int u = 0; u < 8; ++u) ea[u] = ent[k + 8 + u];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) {
+            xs[k + u] = x;
+            x = put_state(x, eb[u]);
+          }
+          k += 8;
+        } while (k + 8 <= cnt);
+      }
+      for (; k < cnt; ++k) {
+        xs[k] = x;
+        x = put_state(x, ent[k]);
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const uint32_t xl = xs[lane];
+    const bool b1 = lane < cnt && xl >= mine.xm, b2 = lane < cnt && (xl >> 8) >= mine.xm;
+    const uint64_t m1 = __ballot(b1), m2 = __ballot(b2);
+    const uint64_t below = (1ull << lane) - 1ull;
+    uint8_t* at = out - (__popcll(m1 & below) + __popcll(m2 & below));
+    if (b1) at[-1] = (uint8_t)xl;
+    if (b2) at[-2] = (uint8_t)(xl >> 8);
+    out -= __popcll(m1) + __popcll(m2);
+  }
+  if (lane == 0) A.lane_len[SL] = (uint32_t)((A.slots + slot_end) - put_end(x, out));
+}
+
+// One thread per stream (lane L, stream k: index L K + k), PUT_BATCH symbols
+// at a time, the next in flight: a wave waits for a line of 32 symbols from
+// HBM once in two rounds, and a round is longer than that takes. Bound by
+// the 29 instructions of a symbol on a wave alone on its SIMD: 132 us for the
+// large batch (it took 224 us with a branch and up to two byte stores each).
 __global__ void __launch_bounds__(64) k_rans_enc(RansEncArgs A) {
+  __shared__ __align__(16) uint8_t shed[64 * PUT_STRIDE];
   const int64_t SL = (int64_t)blockIdx.x * 64 + threadIdx.x;
   if (SL >= A.n_streams) return;
   const StreamGeom G = stream_geom(A, SL);
   const int64_t slot_end = G.D.slot_base + A.K * (6 * G.lane_px_off + 8 * (int64_t)G.q) +
                            (G.kk + 1) * lane_slot_bytes((int64_t)G.Hl * G.Wl);
   uint8_t* out = A.slots + slot_end;
+  PutWindow win{shed + (threadIdx.x + 1) * PUT_STRIDE, 0u};
   const uint4* src = (const uint4*)(A.rev + G.rev_off);
   const int64_t n = A.lane_len[SL];
   uint32_t x = RANS_X0;
-  constexpr int B = 16;  // symbols per batch; the next batch loads while this one is coded
-  uint32_t va[B], vb[B];
-  int na = 0;
-  for (int64_t p0 = 0;; p0 += B) {
-    const int nb = p0 < n ? (int)min<int64_t>(B, n - p0) : 0;
-    if (nb > 0) {
+  constexpr int B = PUT_BATCH;
+  uint4 nxt[B / 4];
 #pragma unroll
-      for (int k = 0; k < B / 4; ++k) {
-        const uint4 w = src[p0 / 4 + k];
-        vb[4 * k] = w.x;
-        vb[4 * k + 1] = w.y;
-        vb[4 * k + 2] = w.z;
-        vb[4 * k + 3] = w.w;
+  for (int u = 0; u < B / 4; ++u) nxt[u] = n > 0 ? src[u] : make_uint4(0u, 0u, 0u, 0u);
+  for (int64_t p0 = 0; p0 < n; p0 += B) {
+    uint32_t cur[B];
+#pragma unroll
+    for (int u = 0; u < B / 4; ++u) {
+      cur[4 * u] = nxt[u].x;
+      cur[4 * u + 1] = nxt[u].y;
+      cur[4 * u + 2] = nxt[u].z;
+      cur[4 * u + 3] = nxt[u].w;
+    }
+    if (p0 + B < n) {
+#pragma unroll
+      for (int u = 0; u < B / 4; ++u) nxt[u] = src[(p0 + B) / 4 + u];
+    }
+    // a state from 2^23 up stays there, and above every f; streams of a wave
+    // end in different batches
+    const bool grown = x >= RANS_L, whole = p0 + B <= n;
+    if (__ballot(!(grown && whole)) == 0ull) {
+#pragma unroll
+      for (int u = 0; u < B; ++u) put_write(x, cur[u], win, false);
+    } else if (__ballot(!grown) == 0ull) {
+#pragma unroll
+      for (int u = 0; u < B; ++u)
+        if (p0 + u < n) put_write(x, cur[u], win, false);
+    } else {
+      for (int u = 0; u < B; ++u) {
+        // (the symbols move down one place a round: no indexed registers)
+        if (p0 + u < n) put_write(x, cur[0], win, true);
+#pragma unroll
+        for (int v = 0; v + 1 < B; ++v) cur[v] = cur[v + 1];
       }
     }
-    if (na > 0) rans_put(x, out, va, na);
-    if (nb == 0) break;
-#pragma unroll
-    for (int k = 0; k < B; ++k) va[k] = vb[k];
-    na = nb;
+    win.flush(out);
   }
-  // the final state's significant bytes (x >= 1), most significant first
-  do {
-    *--out = (uint8_t)x;
-    x >>= 8;
-  } while (x != 0u);
-  A.lane_len[SL] = (uint32_t)((A.slots + slot_end) - out);
+  A.lane_len[SL] = (uint32_t)((A.slots + slot_end) - put_end(x, out));
 }
 
-// Row streams: one thread per stream (a lane row). Its symbols in decode
-// order are the row's pixels left to right, R, G, B, so in coding order they
-// are read in place from the symbol buffer, backwards.
+// Row streams too many for a wave each: one thread per stream, its symbols
+// read in place from the symbol buffer, backwards
 __global__ void __launch_bounds__(64) k_rans_enc_rows(RansEncArgs A) {
+  __shared__ __align__(16) uint8_t shed[64 * PUT_STRIDE];
   const int64_t SL = (int64_t)blockIdx.x * 64 + threadIdx.x;
   if (SL >= A.n_streams) return;
   const int n = find_img_stream(A.desc, A.n_img, SL);
@@ -444,66 +644,92 @@ __global__ void __launch_bounds__(64) k_rans_enc_rows(RansEncArgs A) {
   const int64_t e = SL - D.stream_base;
   const StreamAt S = stream_at(D, ROW_STREAMS, e);
   uint8_t* out = A.slots + S.slot_end;
+  PutWindow win{shed + (threadIdx.x + 1) * PUT_STRIDE, 0u};
   const uint32_t* row = A.sym + (D.px_base + (int64_t)(S.ly * D.ph + S.r) * D.W + (int64_t)S.lx * D.pw) * 3;
   uint32_t x = RANS_X0;
-  constexpr int B = 16;
+  constexpr int B = PUT_BATCH;
   uint32_t v[B];
   for (int k = 3 * S.Wl - 1; k >= 0; k -= B) {
     const int nb = min(B, k + 1);
 #pragma unroll
     for (int m = 0; m < B; ++m) v[m] = m < nb ? row[k - m] : 0u;
-    rans_put(x, out, v, nb);
+#pragma unroll
+    for (int m = 0; m < B; ++m)
+      if (m < nb) put_write(x, v[m], win, true);
+    win.flush(out);
   }
-  // the final state's significant bytes (x >= 1), most significant first
-  do {
-    *--out = (uint8_t)x;
-    x >>= 8;
-  } while (x != 0u);
-  A.lane_len[SL] = (uint32_t)((A.slots + S.slot_end) - out);
+  A.lane_len[SL] = (uint32_t)((A.slots + S.slot_end) - put_end(x, out));
 }
 
 // ------------------------------------------------------------------ container assembly
-// per image: lane_end (inclusive prefix of lane lengths), container bytes
-__global__ void __launch_bounds__(256) k_lane_scan(PackArgs A) {
-  __shared__ uint32_t part[256];
-  __shared__ uint32_t carry;
+// inclusive sum over the wave's lanes
+NXD uint64_t wave_scan(uint64_t v, int lane) {
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint64_t u = __shfl_up(v, d, 64);
+    if (lane >= d) v += u;
+  }
+  return v;
+}
+
+// per image: lane_end (inclusive prefix of lane lengths), container bytes.
+// SCAN_THREADS streams a round: sums within each wave by lane shuffles, then
+// over the waves through LDS (two barriers a round; the large
+// batch's 30,720 streams took 43 us with 256 threads and a barrier a doubling,
+// under 10 us so)
+constexpr int SCAN_THREADS = 1024;
+__global__ void __launch_bounds__(SCAN_THREADS) k_lane_scan(PackArgs A) {
+  __shared__ uint32_t part[SCAN_THREADS / 64];
   const int n = blockIdx.x;
   const ImgDesc D = A.desc[n];
-  const int nl = (int)image_streams(A.K, D.H, D.nlx, D.nly);  // streams of this image
+  const int64_t nl = image_streams(A.K, D.H, D.nlx, D.nly);  // streams of this image
   const int64_t sbase = D.stream_base;
-  if (threadIdx.x == 0) carry = 0;
-  __syncthreads();
-  for (int b0 = 0; b0 < nl; b0 += 256) {
-    const int q = b0 + threadIdx.x;
-    const uint32_t v = q < nl ? A.lane_len[sbase + q] : 0u;
-    part[threadIdx.x] = v;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  uint32_t carry = 0;
+  for (int64_t b0 = 0; b0 < nl; b0 += SCAN_THREADS) {
+    const int64_t q = b0 + threadIdx.x;
+    const uint32_t s = (uint32_t)wave_scan(q < nl ? A.lane_len[sbase + q] : 0u, lane);
+    if (lane == 63) part[wv] = s;
     __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {
-      const uint32_t add = threadIdx.x >= off ? part[threadIdx.x - off] : 0u;
-      __syncthreads();
-      part[threadIdx.x] += add;
-      __syncthreads();
+    uint32_t before = carry, all = 0;
+#pragma unroll
+    for (int w = 0; w < SCAN_THREADS / 64; ++w) {
+      before += w < wv ? part[w] : 0u;
+      all += part[w];
     }
-    if (q < nl) A.lane_end[sbase + q] = carry + part[threadIdx.x];
-    __syncthreads();
-    if (threadIdx.x == 255) carry += part[255];
+    if (q < nl) A.lane_end[sbase + q] = before + s;
+    carry += all;
     __syncthreads();
   }
-  if (threadIdx.x == 0) A.img_bytes[n] = (uint64_t)HDR_BYTES + 4ull * nl + carry;  // nl = streams
+  if (threadIdx.x == 0) A.img_bytes[n] = (uint64_t)HDR_BYTES + 4ull * (uint64_t)nl + carry;  // nl = streams
 }
 
-__global__ void k_img_scan(PackArgs A) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// the containers' offsets, one wave
+__global__ void __launch_bounds__(64) k_img_scan(PackArgs A) {
+  const int lane = threadIdx.x;
   uint64_t acc = 0;
-  for (int n = 0; n < A.n_img; ++n) {
-    A.out_offsets[n] = acc;
-    acc += A.img_bytes[n];
+  for (int n0 = 0; n0 < A.n_img; n0 += 64) {
+    const int n = n0 + lane;
+    const uint64_t v = n < A.n_img ? A.img_bytes[n] : 0ull;
+    const uint64_t s = wave_scan(v, lane);
+    if (n < A.n_img) A.out_offsets[n] = acc + s - v;
+    acc += __shfl(s, 63, 64);
   }
-  A.out_offsets[A.n_img] = acc;
-  *A.overflow = acc > A.out_cap ? 1 : 0;
+  if (lane == 0) {
+    A.out_offsets[A.n_img] = acc;
+    *A.overflow = acc > A.out_cap ? 1 : 0;
+  }
 }
 
-// one 64-thread block per stream: payload copy, stream table entry, header
+// 16 bytes at any address (byte alignment: the hardware splits what it must)
+struct __attribute__((packed)) Bytes16 {
+  uint32_t w[4];
+};
+
+// 64-thread blocks (stream, part): payload copy, 16 bytes a lane, parts of
+// PACK_PART bytes; the stream's first block writes its table entry, the
+// image's first the header
+constexpr uint32_t PACK_PART = 8192;
 __global__ void __launch_bounds__(64) k_pack(PackArgs A) {
   if (*A.overflow) return;
   const int64_t SL = blockIdx.x;
@@ -519,7 +745,13 @@ __global__ void __launch_bounds__(64) k_pack(PackArgs A) {
   uint8_t* C = A.out + A.out_offsets[n];
   uint8_t* dst = C + HDR_BYTES + 4 * ns + (end - len);
   const uint8_t* src = A.slots + slot_end - len;
-  for (uint32_t k = threadIdx.x; k < len; k += 64) dst[k] = src[k];
+  for (uint64_t p0 = (uint64_t)blockIdx.y * PACK_PART; p0 < len; p0 += (uint64_t)gridDim.y * PACK_PART) {
+    const uint64_t p1 = p0 + PACK_PART < len ? p0 + PACK_PART : len;
+    uint64_t k = p0 + 16 * threadIdx.x;
+    for (; k + 16 <= p1; k += 16 * 64) *(Bytes16*)(dst + k) = *(const Bytes16*)(src + k);
+    for (; k < p1; ++k) dst[k] = src[k];
+  }
+  if (blockIdx.y != 0) return;
   if (threadIdx.x < 4) C[HDR_BYTES + 4 * entry + threadIdx.x] = (uint8_t)(end >> (8 * threadIdx.x));
   if (entry == 0 && threadIdx.x == 0) {
     uint8_t h[HDR_BYTES];
@@ -1695,14 +1927,18 @@ hipError_t launch_sample(int h, int C, const DecArgs& a, int grid, int waves, hi
 template <int O, int K>
 static void launch_layout(const RansEncArgs& a, hipStream_t s) {
   hipLaunchKernelGGL((k_rans_counts<O, K>), dim3((unsigned)(a.n_lanes * K)), dim3(64), 0, s, a);
-  const unsigned chunks = (unsigned)((a.max_lane_px + SCATTER_PX - 1) / SCATTER_PX);
-  hipLaunchKernelGGL((k_rans_scatter<O, K>), dim3((unsigned)a.n_lanes, chunks > 0 ? chunks : 1u), dim3(256), 0, s, a);
+  const unsigned chunks =
+      (unsigned)std::max<int64_t>(1, std::min<int64_t>((a.max_lane_px + SCATTER_PX - 1) / SCATTER_PX, 65535));
+  hipLaunchKernelGGL((k_rans_scatter<O, K>), dim3((unsigned)a.n_lanes, chunks), dim3(256), 0, s, a);
 }
 
 hipError_t launch_rans_encode(const RansEncArgs& a, hipStream_t s) {
   if (a.n_lanes == 0) return hipSuccess;
   if (a.K == ROW_STREAMS) {
-    hipLaunchKernelGGL(k_rans_enc_rows, dim3((unsigned)((a.n_streams + 63) / 64)), dim3(64), 0, s, a);
+    if (a.wave_per_stream)
+      hipLaunchKernelGGL(k_rans_enc_wave<true>, dim3((unsigned)a.n_streams), dim3(64), 0, s, a);
+    else
+      hipLaunchKernelGGL(k_rans_enc_rows, dim3((unsigned)((a.n_streams + 63) / 64)), dim3(64), 0, s, a);
     return hipGetLastError();
   }
   if (a.h < 1 || a.h > 3 || !valid_interleave(a.K)) return hipErrorInvalidValue;
@@ -1726,15 +1962,23 @@ hipError_t launch_rans_encode(const RansEncArgs& a, hipStream_t s) {
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const int grid = (int)((a.n_streams + 63) / 64);
-  hipLaunchKernelGGL(k_rans_enc, dim3(grid), dim3(64), 0, s, a);
+  if (a.wave_per_stream)
+    hipLaunchKernelGGL(k_rans_enc_wave<false>, dim3((unsigned)a.n_streams), dim3(64), 0, s, a);
+  else
+    hipLaunchKernelGGL(k_rans_enc, dim3((unsigned)((a.n_streams + 63) / 64)), dim3(64), 0, s, a);
   return hipGetLastError();
 }
 
 hipError_t launch_pack(const PackArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(k_lane_scan, dim3(a.n_img), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(k_lane_scan, dim3(a.n_img), dim3(SCAN_THREADS), 0, s, a);
   hipLaunchKernelGGL(k_img_scan, dim3(1), dim3(64), 0, s, a);
-  if (a.n_streams > 0) hipLaunchKernelGGL(k_pack, dim3((unsigned)a.n_streams), dim3(64), 0, s, a);
+  if (a.n_streams > 0) {
+    // a stream's bytes are at most two per symbol; a lane's symbols spread
+    // over its K streams (row streams: a row of them)
+    const int64_t parts = (a.max_stream_bytes + PACK_PART - 1) / PACK_PART;
+    hipLaunchKernelGGL(k_pack, dim3((unsigned)a.n_streams, (unsigned)std::max<int64_t>(1, std::min<int64_t>(parts, 64))),
+                       dim3(64), 0, s, a);
+  }
   return hipGetLastError();
 }
 

@@ -43,7 +43,20 @@ struct RansEncArgs {
   int32_t* after;          // per stream and step t: the stream's symbols in steps after t;
                            // from desc[n].after_base, stream_after_entries each
   int64_t max_lane_px;     // pixels of the largest lane
+  int wave_per_stream;     // a wave per stream, else a thread (rans_wave)
 };
+
+// Whether each rANS stream is coded by a wave of its own. A wave per stream
+// takes 89 cycles a symbol while it has its SIMD to itself, and about 65 times
+// the waves of the SIMD beyond (4 cycles an instruction); a thread per stream
+// 320 to 410, whatever their number (measured, streams of 768 to 1,024
+// symbols of unequal length). So the wave is ahead up to about five streams on
+// each of the 4 SIMDs of a CU; the line is at four. Row streams have no pass
+// that lays their symbols out: a thread reads a row of its own, and the wave
+// stays ahead for longer.
+inline bool rans_wave(int64_t n_streams, bool rows, int cus) {
+  return n_streams <= (rows ? 8 : 4) * 4 * (int64_t)cus;
+}
 
 struct PackArgs {
   const ImgDesc* desc;
@@ -61,6 +74,7 @@ struct PackArgs {
   uint64_t* out_offsets;   // n_img + 1
   uint64_t out_cap;
   int32_t* overflow;       // set when the containers would exceed out_cap
+  int64_t max_stream_bytes;  // an estimate of the longest stream, for the grid
 };
 
 struct DecArgs {
