@@ -303,10 +303,7 @@ nellox_status run_pass(nellox_model* m, const Plan& P, uint8_t* ws, const WsLayo
   a.sym = sym;
   a.bits = bits;
   a.cdf = cdf;
-  const int64_t waves = (P.n_tiles + 0);
-  int grid = persistent_grid(m);
-  const int64_t need = (waves + 7) / 8;
-  if (need < grid) grid = (int)std::max<int64_t>(need, 1);
+  const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(P.n_tiles, persistent_grid(m)));
   hipError_t e = launch_pass(m->h, m->Cp, a, grid, s);
   if (e != hipSuccess) return hip_fail(e, "full-image pass launch");
   return NELLOX_OK;

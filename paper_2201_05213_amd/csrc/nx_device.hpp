@@ -73,12 +73,18 @@ NXD float xtanh(float x) {
 
 // ELU with exp(x) - 1 from the hardware exp2 for x <= 0: the rounding of
 // x log2(e) costs a relative error of at most |x| 2^-24 ln2 in exp(x), i.e.
-// an absolute error below 3e-8 in the activation. For x > 0 the exponent is
-// 0 and e = 0; for x <= 0, exp(x) - 1 >= x, so the larger of x and e is the
-// activation (x itself where rounding put e below it, |x| < 2^-23)
+// an absolute error below 3e-8 in the activation. 1 - exp(x), clamped to
+// [0, 1] by the subtraction's output modifier, is 0 for x > 0 and its negative
+// is the activation for x <= 0, where exp(x) - 1 >= x; so the larger of x and
+// that is the activation (x itself where rounding put it above, |x| < 2^-23).
+// The maximum is a median with infinity (a value the compiler does not see:
+// it would make it a maximum, prefaced with a quieting v_max of x): 4
+// instructions where min, max and their quieting took 6.
 NXD float xelu(float x) {
-  const float e = __builtin_amdgcn_exp2f(fminf(x, 0.0f) * kLog2e) - 1.0f;
-  return fmaxf(x, e);
+  float inf = INFINITY;
+  asm("" : "+s"(inf));
+  const float c = __builtin_amdgcn_fmed3f(1.0f - __builtin_amdgcn_exp2f(x * kLog2e), 0.0f, 1.0f);
+  return __builtin_amdgcn_fmed3f(x, -c, inf);
 }
 
 // logistic sigmoid: monotone non-decreasing in z because the hardware exp2
@@ -160,12 +166,36 @@ struct TapCodes {
 typedef const __attribute__((address_space(1))) uint8_t* gbytes;
 NXD gbytes as_global(const uint8_t* p) { return (gbytes)p; }
 
+// Which of a lane group's taps lie inside the lane (bit kc: the tap of
+// K-chunk kc), by what is cut off around the pixel: n columns of the window
+// at its left, n at its right, n rows at its top (n = 0 .. H_).
+struct TapMasks {
+  uint32_t cut[3][4][4];  // [left, right, top][n][lane group]
+};
+template <int H_>
+constexpr TapMasks tap_masks() {
+  TapMasks M{};
+  constexpr int K = 2 * H_ + 1;
+  for (int n = 0; n <= H_; ++n)
+    for (int g = 0; g < 4; ++g)
+      for (int kc = 0; kc < conv_chunks(H_); ++kc) {
+        const int tap = (4 * kc + g) / 3;
+        const int dy = tap < H_ * K ? tap / K : H_, dx = tap - K * dy;
+        if (dx >= n) M.cut[0][n][g] |= 1u << kc;
+        if (dx <= 2 * H_ - n) M.cut[1][n][g] |= 1u << kc;
+        if (dy >= n) M.cut[2][n][g] |= 1u << kc;
+      }
+  return M;
+}
+template <int H_>
+__device__ const TapMasks tap_masks_of = tap_masks<H_>();
+
 // Every tap is loaded from a position clamped into the lane (always in
 // bounds), then taps outside the lane are replaced by 0: no branch around the
 // loads, so all of them are in flight together.
 template <int H_>
-NXD void gather(float (&ctx)[conv_chunks(H_)], const TapCodes<H_>& tc, const uint8_t* img, int W, int y0, int x0,
-                int Hl, int Wl, int i, int j, bool active) {
+NXD void gather_clamped(float (&ctx)[conv_chunks(H_)], const TapCodes<H_>& tc, const uint8_t* img, int W, int y0,
+                        int x0, int Hl, int Wl, int i, int j) {
   const gbytes gimg = as_global(img);
   uint32_t raw[conv_chunks(H_)];
 #pragma unroll
@@ -181,10 +211,67 @@ NXD void gather(float (&ctx)[conv_chunks(H_)], const TapCodes<H_>& tc, const uin
     const int dy = (int)(code & 3u), dx = (int)((code >> 2) & 7u);
     const int y = i - H_ + dy, x = j - H_ + dx;
     // inside the lane, as a bit mask (no short-circuit, no branch)
-    const int ok = -(int)(((unsigned)y < (unsigned)Hl) & ((unsigned)x < (unsigned)Wl) & (unsigned)active);
+    const int ok = -(int)(((unsigned)y < (unsigned)Hl) & ((unsigned)x < (unsigned)Wl));
     // normalise() of the tap, with the numerator masked: padding is exactly 0
     const int num = (2 * (int)raw[kc] - 255) & ok;
     ctx[kc] = (float)num * (1.0f / 255.0f);
+  }
+}
+
+// The same contexts with an address per row of the window instead of one per
+// tap. The bytes of a window row are contiguous and are the inputs k = R dy
+// .. R dy + R - 1 in order (R = 3 (2 H_ + 1)), so the tap of K-chunk kc sits
+// at the lane's row address plus a constant (the instruction's offset); a
+// chunk that straddles two rows picks one of two addresses by lane group.
+// Bytes outside the lane but inside the image are read and dropped (rows
+// above the image: row 0 is read). In an image of at least H_ columns the
+// only window positions outside its memory are those left of its first row
+// and, with one row, right of it; a wave with such a pixel takes the clamped
+// form. ytop: a row of the image (wave-uniform) at or above every pixel's, by
+// fewer than 64 rows. The context of a pixel outside the lane (a tile's or
+// group's unused rows) is that of a pixel in it. A tap costs 3 instructions here (a border pixel's 5), 28 in
+// the clamped form: 504 of the about 2,200 of a tile of the full-image pass.
+template <int H_>
+NXD void gather(float (&ctx)[conv_chunks(H_)], const TapCodes<H_>& tc, const uint8_t* img, int W, int y0, int x0,
+                int Hl, int Wl, int i, int j, int ytop) {
+  constexpr int R = 3 * (2 * H_ + 1);
+  const int ic = min(i, Hl - 1), jc = min(max(j, 0), Wl - 1);
+  const int Y = y0 + ic, X = x0 + jc;
+  if (__ballot((Y <= H_ && X < H_) || (Y == 0 && X + H_ >= W) || W < H_) != 0ull) {
+    gather_clamped<H_>(ctx, tc, img, W, y0, x0, Hl, Wl, ic, jc);
+    return;
+  }
+  const int g = (threadIdx.x >> 4) & 3;
+  const int top = __builtin_amdgcn_readfirstlane(max(ytop - H_, 0));
+  const gbytes base = as_global(img + (int64_t)top * W * 3);
+  const uint32_t col = 3u * (uint32_t)X + (uint32_t)g;
+  uint32_t row[H_ + 1];
+#pragma unroll
+  for (int dy = 0; dy <= H_; ++dy)
+    row[dy] = __umul24((uint32_t)(max(Y - H_ + dy, 0) - top), 3u * (uint32_t)W) + col;
+  uint32_t raw[conv_chunks(H_)];
+#pragma unroll
+  for (int kc = 0; kc < conv_chunks(H_); ++kc) {
+    const int d0 = min(4 * kc / R, H_), d1 = min((4 * kc + 3) / R, H_);
+    const int c0 = 4 * kc - R * d0 - 3 * H_, c1 = 4 * kc - R * d1 - 3 * H_;
+    if (d0 == d1)
+      raw[kc] = (base + c0)[row[d0]];
+    else
+      raw[kc] = (base + c1)[4 * kc + g >= R * d1 ? row[d1] : row[d0] + (uint32_t)(c0 - c1)];
+  }
+  const int nl = max(H_ - jc, 0), nr = max(jc + H_ - (Wl - 1), 0), nt = max(H_ - ic, 0);
+  if (__ballot((nl | nr | nt) != 0) == 0ull) {
+#pragma unroll
+    for (int kc = 0; kc < conv_chunks(H_); ++kc)
+      ctx[kc] = __builtin_fmaf(2.0f, (float)raw[kc], -255.0f) * (1.0f / 255.0f);
+  } else {
+    const TapMasks& M = tap_masks_of<H_>;
+    const uint32_t m = M.cut[0][min(nl, H_)][g] & M.cut[1][min(nr, H_)][g] & M.cut[2][min(nt, H_)][g];
+#pragma unroll
+    for (int kc = 0; kc < conv_chunks(H_); ++kc) {
+      const float v = __builtin_fmaf(2.0f, (float)raw[kc], -255.0f) * (1.0f / 255.0f);
+      ctx[kc] = __int_as_float(__float_as_int(v) & __builtin_amdgcn_sbfe((int)m, kc, 1));
+    }
   }
 }
 

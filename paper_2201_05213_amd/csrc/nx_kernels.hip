@@ -149,24 +149,30 @@ __global__ void __launch_bounds__(NWAVES * 64) k_pass(PassArgs A) {
   load_weights(w, A.w, A.wfloats);
   const int lane = threadIdx.x & 63, p = lane & 15, g = lane >> 4;
   const bool has2 = g < 2;
-  const int64_t gw = (int64_t)blockIdx.x * NWAVES + (threadIdx.x >> 6);
+  // a batch of at most a tile per wave is dealt to the workgroups first, so
+  // that it spreads over the CUs; else a workgroup takes tiles side by side
   const int64_t nwv = (int64_t)gridDim.x * NWAVES;
+  const int wv = uniform((int)(threadIdx.x >> 6));
+  const int64_t gw = A.n_tiles <= nwv ? (int64_t)wv * gridDim.x + blockIdx.x : (int64_t)blockIdx.x * NWAVES + wv;
   TapCodes<H_> tc;
   tc.init(g);
   for (int64_t t = gw; t < A.n_tiles; t += nwv) {
     tc.refresh();
     const int n = find_img_uniform(A.desc, A.n_img, t, false);
     const ImgDesc D = uniform_desc(A.desc + n);
-    const int64_t tt = t - D.tile_base;
-    const int y = (int)(tt / D.ntx);
-    const int xraw = (int)(tt - (int64_t)y * D.ntx) * 16 + p;
+    const uint32_t tt = (uint32_t)(t - D.tile_base);  // < 65535 x 4096
+    const int y = uniform((int)(tt / (uint32_t)D.ntx));
+    const int xraw = (int)(tt - (uint32_t)y * (uint32_t)D.ntx) * 16 + p;
     const bool active = xraw < D.W;
     const int x = active ? xraw : D.W - 1;
-    const int ly = y / D.ph, lx = x / D.pw;
+    // y / ph and x / pw by float quotients: (v + 0.5) / d is at least 0.5 / d
+    // from an integer, the error below 2^-22 v / d with v < 2^16
+    const int ly = uniform((int)(((float)y + 0.5f) * __builtin_amdgcn_rcpf((float)D.ph)));
+    const int lx = (int)(((float)x + 0.5f) * __builtin_amdgcn_rcpf((float)D.pw));
     const int y0 = ly * D.ph, x0 = lx * D.pw;
     const int Hl = min(D.ph, D.H - y0), Wl = min(D.pw, D.W - x0);
     float ctx[conv_chunks(H_)];
-    gather<H_>(ctx, tc, D.px, D.W, y0, x0, Hl, Wl, y - y0, x - x0, active);
+    gather<H_>(ctx, tc, D.px, D.W, y0, x0, Hl, Wl, y - y0, x - x0, y);
     f4 head[HEAD_TILES];
     net_forward<H_, C_>(lds_weights(w), A.nb, ctx, head, lane);
     Mix M;
@@ -485,8 +491,8 @@ NXD uint8_t* put_end(uint32_t x, uint8_t* out) {
 // symbol: its symbols come from LDS 8 ahead, and the states go back there),
 // and the lanes write the bytes their symbols shed, placed by counting the
 // lanes before them. Chosen while the waves of a SIMD are few (rans_wave).
-// 196,608 symbols in one stream: 36.7 ms with a chain that divided by a
-// float quotient and moved its own bytes, MEASURED_WAVE.
+// 196,608 symbols in one stream: 36.7 ms (448 cycles a symbol) with a chain
+// that divided by a float quotient and moved its own bytes, 7.3 ms (89) so.
 template <bool ROWS>
 __global__ void __launch_bounds__(64) k_rans_enc_wave(RansEncArgs A) {
   __shared__ PutSym ent[64 + 16];  // the last 16 are read ahead, never coded
@@ -1223,7 +1229,7 @@ __device__ void decode_lane(const DecArgs& A, const float* w, uint32_t* piv, int
       if constexpr (shear)
         gather_ring<H_>(ctx, tc, ring, rows, (int)gi, min(i, Hl - 1), active);
       else
-        gather<H_>(ctx, tc, img, D.W, y0, x0, Hl, Wl, i, j, active);
+        gather<H_>(ctx, tc, img, D.W, y0, x0, Hl, Wl, i, j, y0 + ts);
       // sampling: the slots of pixel p (every lane group draws the same)
       uint32_t sl[3] = {0u, 0u, 0u};
       if constexpr (SAMPLE) sample_slots(D.seed, D.W, y0 + i, x0 + j, sl);

@@ -193,7 +193,7 @@ __global__ void __launch_bounds__(TRAIN_WAVES * 64) k_train_fwd(TrainArgs A) {
     const TileCoord T = tile_coord(A, t, p);
     const uint8_t* img = A.imgs + (int64_t)T.n * A.H * A.W * 3;
     float ctx[KC];
-    gather<H_>(ctx, tc, img, A.W, 0, 0, A.H, A.W, T.y, T.x, T.active);
+    gather<H_>(ctx, tc, img, A.W, 0, 0, A.H, A.W, T.y, T.x, T.y);
     if (!synced) {
       __syncthreads();
       synced = true;
