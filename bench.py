@@ -38,7 +38,7 @@ DECODE_TRAFFIC = {
     "sheared": {"src_sha": "fd38217a5f6439eb", "patch": (82, 64), "interleave": 16,
                 "fetch_kib": 38035.7, "write_kib": 748684.8, "fetch_scale": 1.99982, "write_scale": 1.0},
 }
-KERNEL_SOURCES = ("nx_kernels.hip", "nx_device.hpp", "nx_layout.hpp", "nx_kernels.hpp", "nx_order.hpp")
+KERNEL_SOURCES = ("nx_kernels.hip", "nx_team.hip", "nx_coder.hpp", "nx_device.hpp", "nx_layout.hpp", "nx_kernels.hpp", "nx_order.hpp")
 
 
 def kernel_sources_sha() -> str:

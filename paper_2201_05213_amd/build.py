@@ -8,7 +8,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libnellox.so")
-SOURCES = [os.path.join(HERE, "csrc", f) for f in ("nx_kernels.hip", "nx_train.hip", "nx_capi.cpp")]
+SOURCES = [os.path.join(HERE, "csrc", f) for f in ("nx_kernels.hip", "nx_team.hip", "nx_train.hip", "nx_capi.cpp")]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950",
@@ -28,6 +28,7 @@ HIPCC_FLAGS = [
 # LLVM's iterative ILP scheduler orders their instructions with more overlap
 # than the default one (the arithmetic and its order are unchanged)
 SOURCE_FLAGS = {"nx_kernels.hip": ["-mllvm", "-amdgpu-sched-strategy=iterative-ilp"],
+                "nx_team.hip": ["-mllvm", "-amdgpu-sched-strategy=iterative-ilp"],
                 "nx_train.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]}
 
 

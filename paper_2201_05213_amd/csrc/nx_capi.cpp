@@ -63,6 +63,7 @@ struct nellox_model {
   int64_t wfloats;
   int device;
   int num_cu;
+  size_t lds;           // LDS of one workgroup
   std::mutex mu;        // guards the staging buffer
   void* staging;        // pinned host memory for per-call plans
   size_t staging_bytes;
@@ -461,6 +462,7 @@ nellox_status nellox_model_create(const void* blob, size_t nbytes, nellox_model*
   m->wfloats = (int64_t)img.size();
   m->device = dev;
   m->num_cu = prop.multiProcessorCount;
+  m->lds = prop.sharedMemPerBlock;
   m->staging = nullptr;
   m->staging_bytes = 0;
   e = hipMalloc(&m->dw, img.size() * 4);
@@ -641,15 +643,21 @@ static nellox_status prepare_impl(nellox_model* m, int32_t n, const nellox_image
   plan->waves = std::max(waves, 1);
   plan->grid = grid;
   plan->ring_offset = W.ring;
-  plan->ring_rows = P.ring_rows;
+  plan->ring_rows = ring_rows_for(P.ph_max, m->h);
   plan->n_lanes = P.n_lanes;
   plan->model_hash = m->hash;
   plan->ws_bytes = W.small;
   plan->desc_offset = W.desc;
   plan->counter_offset = W.flags + 4;
-  hipError_t e = prepare_decode(m->h, m->Cp, P.K);
+  hipError_t e = P.K == ROW_STREAMS ? hipSuccess : prepare_decode(m->h, m->Cp, P.K);
+  if (e == hipSuccess) e = prepare_team(m->h, m->Cp, P.K == ROW_STREAMS);
   if (e != hipSuccess) return hip_fail(e, "decoder set-up");
   return NELLOX_OK;
+}
+
+// lanes per CU decoded by teams of waves, 0: a wave per lane
+static int teams_of(const nellox_model* m, int64_t n_lanes, int order, int64_t rows) {
+  return decode_teams(m->h, m->Cp, m->wfloats, n_lanes, order, rows, m->num_cu, m->lds);
 }
 
 static nellox_status run_impl(nellox_model* m, const nellox_decode_plan* plan, const uint8_t* in,
@@ -699,6 +707,9 @@ static nellox_status run_impl(nellox_model* m, const nellox_decode_plan* plan, c
   if (rows) {
     a.K = ROW_STREAMS;
     e = launch_decode_rows(m->h, m->Cp, a, plan->grid, s);
+  } else if (const int teams = teams_of(m, plan->n_lanes, plan->order, plan->ring_rows)) {
+    a.team_rows = (int)plan->ring_rows;
+    e = launch_decode_team(m->h, m->Cp, a, teams, false, s);
   } else {
     e = launch_decode(m->h, m->Cp, a, plan->grid, plan->waves, s);
   }
@@ -783,7 +794,9 @@ nellox_status nellox_sample(const nellox_model* mc, int32_t n, const uint64_t* s
   for (int k = 0; k < n; ++k) P.d[k].seed = seeds[k];
   hipStream_t s = (hipStream_t)stream;
   uint8_t* w8 = (uint8_t*)ws;
-  hipError_t e = prepare_decode(m->h, m->Cp, 4);
+  const int64_t rows = ring_rows_for(P.ph_max, m->h);
+  const int teams = teams_of(m, P.n_lanes, o->order, rows);
+  hipError_t e = teams ? prepare_team(m->h, m->Cp, false) : prepare_decode(m->h, m->Cp, 4);
   if (e != hipSuccess) return hip_fail(e, "sampler set-up");
   if ((st = upload_plan(m, P, w8, W, s))) return st;
   int32_t* counter = (int32_t*)(w8 + W.flags + 4);
@@ -804,7 +817,8 @@ nellox_status nellox_sample(const nellox_model* mc, int32_t n, const uint64_t* s
   a.ring_rows = (int)P.ring_rows;
   int grid = 0, waves = 0;
   decode_shape(P.n_lanes, persistent_grid(m), grid, waves);
-  e = launch_sample(m->h, m->Cp, a, grid, waves, s);
+  a.team_rows = (int)rows;
+  e = teams ? launch_decode_team(m->h, m->Cp, a, teams, true, s) : launch_sample(m->h, m->Cp, a, grid, waves, s);
   if (e != hipSuccess) return hip_fail(e, "sampler launch");
   return NELLOX_OK;
 }

@@ -275,42 +275,6 @@ NXD void gather(float (&ctx)[conv_chunks(H_)], const TapCodes<H_>& tc, const uin
   }
 }
 
-// gather() shared by the NW waves of a workgroup that all need the same
-// tile's contexts: wave wv loads and normalises the K-chunks kc = wv, wv + NW,
-// ... (the same positions, clamps and masks as gather(), tap offsets computed
-// from the chunk index), writes them to LDS (cb: 64 lanes x gather_stride
-// floats), and after a barrier every wave reads all of them. Every wave of
-// the workgroup must call it.
-template <int H_>
-constexpr int gather_stride() { return (conv_chunks(H_) + 3) / 4 * 4; }
-template <int H_, int NW>
-NXD void gather_shared(float (&ctx)[conv_chunks(H_)], const uint8_t* img, int W, int y0, int x0, int Hl, int Wl,
-                       int i, int j, bool active, int wv, float* cb, int lane) {
-  constexpr int KC = conv_chunks(H_), KW = 2 * H_ + 1, CS = gather_stride<H_>();
-  const int g = lane >> 4;
-  const gbytes gimg = as_global(img);
-  float v[(KC + NW - 1) / NW];
-#pragma unroll
-  for (int k = 0; k < (KC + NW - 1) / NW; ++k) {
-    const int kc = min(wv + NW * k, KC - 1);
-    const int kk = 4 * kc + g, tap = kk / 3, ch = kk - 3 * tap;
-    const int dy = tap < H_ * KW ? tap / KW : H_;
-    const int dx = tap < H_ * KW ? tap - KW * dy : tap - H_ * KW;
-    const int y = i - H_ + dy, x = j - H_ + dx;
-    const int yc = min(max(y, 0), Hl - 1), xc = min(max(x, 0), Wl - 1);
-    const uint32_t raw = gimg[((int64_t)(y0 + yc) * W + (x0 + xc)) * 3 + ch];
-    const int ok = -(int)(((unsigned)y < (unsigned)Hl) & ((unsigned)x < (unsigned)Wl) & (unsigned)active);
-    const int num = (2 * (int)raw - 255) & ok;
-    v[k] = (float)num * (1.0f / 255.0f);
-  }
-#pragma unroll
-  for (int k = 0; k < (KC + NW - 1) / NW; ++k)
-    if (wv + NW * k < KC) cb[lane * CS + wv + NW * k] = v[k];
-  __syncthreads();
-#pragma unroll
-  for (int kc = 0; kc < KC; ++kc) ctx[kc] = cb[lane * CS + kc];
-}
-
 // Context of pixel (i, t) of a lane from its sheared canvas window (Sec. 3.1,
 // Algorithm 2): tap (dy, dx) of the causal kernel is row i - h + dy, sheared
 // column t - h(h+2) + (h+1) dy + dx, always a column before t. The window
@@ -437,125 +401,6 @@ NXD void net_forward(const float* __restrict__ w, int nb, const float (&ctx)[con
   sink(2 * nb, u);
   bias_init(head, bias_head, g);
   layer_mm<HEAD_TILES, MT>(w_head, u, head, lane);
-}
-
-// The network of one 16-pixel tile computed by the NW waves of a workgroup
-// together: wave wv computes the output tiles mt with mt % NW == wv of every
-// layer and the head tiles likewise, and the activations each 1x1 layer
-// reads are exchanged through LDS (xb: two buffers of C/16 tiles x 64 lanes x
-// 4 floats, used in turn), so every wave holds all input tiles. Each output
-// element is the chain of MFMAs net_forward computes for it, in the same k
-// order, so the values are bitwise the same. The head rows go to
-// hb[pixel * 128 + row] (the weight image's permuted row order). Every wave
-// of the workgroup must call it: it holds barriers, and its last one makes
-// hb readable by all.
-template <int H_, int C_, int NW>
-NXD void net_forward_split(const float* __restrict__ w, int nb, const float (&ctx)[conv_chunks(H_)], float* xb,
-                           float* hb, int lane, int wv) {
-  constexpr int MT = C_ / 16;
-  constexpr int KC = conv_chunks(H_), KQ = conv_quads(H_);
-  constexpr int MY = (MT + NW - 1) / NW;  // output tiles per wave (a wave may own none)
-  constexpr int HY = HEAD_TILES / NW;
-  static_assert(HEAD_TILES % NW == 0, "head tiles are dealt evenly");
-  const WeightLayout L = weight_layout(H_, C_, 0);
-  const int g = lane >> 4;
-  const int64_t layer_stride = (int64_t)MT * MT * 256;
-  const float* bias_conv = w + L.head + (int64_t)HEAD_TILES * MT * 256 + 2 * (int64_t)nb * layer_stride;
-  const float* bias_blk = bias_conv + C_;
-  const float* bias_head = bias_blk + 2 * (int64_t)nb * C_;
-  const float* w_head = w + L.layer0 + 2 * (int64_t)nb * layer_stride;
-
-  // out (pre-initialised with the bias) += W in for output tile mt of a
-  // layer (or of the head): k-chunks in the order (ct, q), as layer_mm
-  // (a wave's tile is one dependent MFMA chain, so the layer's weights are
-  // all read from LDS before the chain starts)
-  auto tile_mm = [&](const float* wl, const f4(&in)[MT], f4& out, int mt) {
-    f4 wq[MT];
-#pragma unroll
-    for (int ct = 0; ct < MT; ++ct) wq[ct] = *(const f4*)(wl + (((int64_t)mt * MT + ct) * 64 + lane) * 4);
-#pragma unroll
-    for (int ct = 0; ct < MT; ++ct)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) out = __builtin_amdgcn_mfma_f32_16x16x4f32(wq[ct][q], in[ct][q], out, 0, 0, 0);
-  };
-  int par = 0;
-  auto share = [&](const f4(&u)[MY], f4(&in)[MT]) {
-    float* X = xb + par * (MT * 256);
-#pragma unroll
-    for (int k = 0; k < MY; ++k) {
-      const int mt = wv + NW * k;
-      if (mt < MT) *(f4*)(X + ((int64_t)mt * 64 + lane) * 4) = u[k];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) in[mt] = *(const f4*)(X + ((int64_t)mt * 64 + lane) * 4);
-    par ^= 1;
-  };
-
-  f4 a[MY];
-#pragma unroll
-  for (int k = 0; k < MY; ++k) {
-    const int mt = wv + NW * k;
-    if (mt >= MT) continue;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) a[k][v] = bias_conv[16 * mt + 4 * g + v];
-    f4 wq[KQ];
-#pragma unroll
-    for (int kq = 0; kq < KQ; ++kq) wq[kq] = *(const f4*)(w + (((int64_t)mt * KQ + kq) * 64 + lane) * 4);
-#pragma unroll
-    for (int kq = 0; kq < KQ; ++kq)
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        if (4 * kq + q < KC) a[k] = __builtin_amdgcn_mfma_f32_16x16x4f32(wq[kq][q], ctx[4 * kq + q], a[k], 0, 0, 0);
-  }
-  for (int b = 0; b < nb; ++b) {
-    f4 u[MY], in[MT], z[MY];
-#pragma unroll
-    for (int k = 0; k < MY; ++k)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) u[k][v] = xelu(a[k][v]);
-    share(u, in);
-#pragma unroll
-    for (int k = 0; k < MY; ++k) {
-      const int mt = wv + NW * k;
-      if (mt >= MT) continue;
-      const float* bb = bias_blk + (int64_t)(2 * b) * C_;
-#pragma unroll
-      for (int v = 0; v < 4; ++v) z[k][v] = bb[16 * mt + 4 * g + v];
-      tile_mm(w + L.layer0 + (int64_t)(2 * b) * layer_stride, in, z[k], mt);
-    }
-#pragma unroll
-    for (int k = 0; k < MY; ++k)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) u[k][v] = xelu(z[k][v]);
-    share(u, in);
-#pragma unroll
-    for (int k = 0; k < MY; ++k) {
-      const int mt = wv + NW * k;
-      if (mt >= MT) continue;
-      const float* bb = bias_blk + (int64_t)(2 * b + 1) * C_;
-#pragma unroll
-      for (int v = 0; v < 4; ++v) z[k][v] = bb[16 * mt + 4 * g + v];
-      tile_mm(w + L.layer0 + (int64_t)(2 * b + 1) * layer_stride, in, z[k], mt);
-      a[k] = a[k] + z[k];
-    }
-  }
-  f4 u[MY], in[MT];
-#pragma unroll
-  for (int k = 0; k < MY; ++k)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) u[k][v] = xelu(a[k][v]);
-  share(u, in);
-#pragma unroll
-  for (int k = 0; k < HY; ++k) {
-    const int hm = wv + NW * k;
-    f4 hd;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) hd[v] = bias_head[16 * hm + 4 * g + v];
-    tile_mm(w_head, in, hd, hm);
-    *(f4*)(hb + (lane & 15) * 128 + 16 * hm + 4 * g) = hd;
-  }
-  __syncthreads();
 }
 
 // ------------------------------------------------------------------ mixture
@@ -698,7 +543,7 @@ NXD float dpp_row(float v) {
 }
 constexpr int DPP_SHL1 = 0x101, DPP_SHL2 = 0x102, DPP_SHL4 = 0x104, DPP_SHL8 = 0x108, DPP_BCAST0 = 0x150;
 NXD float row_bcast0(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), DPP_BCAST0, 0xf, 0xf, false));
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), DPP_BCAST0, 0xf, 0xf, true));
 }
 NXD float row16_sum(float t) {
   const float s = (t + dpp_row<DPP_SHL4>(t)) + dpp_row<DPP_SHL8>(t);
@@ -760,11 +605,6 @@ NXD void chan_params16(const Mix16& M, int c, float xr, float xg, Chan16& Q) {
   Q.mu = m;
   Q.a = Q.is * kLog2e;
   Q.b = m * Q.a;
-}
-NXD float cdf_eval16(int k, const Chan16& Q) {
-  const float e = bin_edge(k);
-  const float x = __builtin_amdgcn_exp2f(__builtin_fmaf(-e, Q.a, Q.b));
-  return row16_sum(Q.w * __builtin_amdgcn_rcpf(1.0f + x));
 }
 NXD float posterior16(Mix16& M, int x, const Chan16& Q, bool live) {
   const float t = live ? M.logw + log_bin(x, Q.mu, Q.is) : -INFINITY;

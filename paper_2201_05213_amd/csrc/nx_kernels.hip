@@ -2,20 +2,19 @@
 //   k_pass      full-image pass: every pixel's quantised CDF at its own value
 //               (encoder symbols), or its continuous code length (NLL), or a
 //               full CDF row (debug), 16 pixels per wave on MFMA
-//   k_rans_enc  one thread per lane: rANS-encodes the lane's symbols in
-//               reverse decode order into a private slot
+//   k_rans_*    rANS encoder: symbols laid out in coding order, then a wave
+//               or a thread per stream
 //   k_lane_scan / k_img_scan / k_pack   container assembly
 //   k_decode    persistent decoder: waves pop lanes from a queue and decode
 //               them step by step (wavefront) or pixel by pixel (raster)
+// (with few lanes, or a stream per row: nx_team.hip)
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include <algorithm>
 #include <mutex>
 
-#include "nx_device.hpp"
-#include "nx_kernels.hpp"
-#include "nx_order.hpp"
+#include "nx_coder.hpp"
 
 namespace nx {
 
@@ -26,16 +25,6 @@ constexpr int PRM_STRIDE = 36;            // floats per pixel: (w, a, b) of 12 c
 constexpr int PRM_WORDS = 16 * PRM_STRIDE;  // per decoder wave: one channel's mixtures of 16 pixels
 constexpr int WAVE_LDS_WORDS = PIV_WORDS + PRM_WORDS;
 static_assert(DECODE_LDS_EXTRA == NWAVES_DEC * WAVE_LDS_WORDS * 4, "decoder LDS budget");
-
-NXD int find_img(const ImgDesc* __restrict__ d, int n, int64_t key, bool by_lane) {
-  int lo = 0, hi = n - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    const int64_t b = by_lane ? d[mid].lane_base : d[mid].tile_base;
-    if (b <= key) lo = mid; else hi = mid - 1;
-  }
-  return lo;
-}
 
 // the image holding global stream `key` (by its first stream)
 NXD int find_img_stream(const ImgDesc* __restrict__ d, int n, int64_t key) {
@@ -87,59 +76,6 @@ NXD StreamAt stream_at(const ImgDesc& D, int K, int64_t e) {
   return S;
 }
 
-
-NXD uint32_t rd_u32(const uint8_t* p) {
-  return (uint32_t)p[0] | ((uint32_t)p[1] << 8) | ((uint32_t)p[2] << 16) | ((uint32_t)p[3] << 24);
-}
-
-NXD int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
-NXD int64_t uniform64(int64_t v) {
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)v >> 32));
-  return (int64_t)(((uint64_t)hi << 32) | lo);
-}
-
-// the same search with every step wave-uniform (key must be wave-uniform)
-NXD int find_img_uniform(const ImgDesc* __restrict__ d, int n, int64_t key, bool by_lane = true) {
-  int lo = 0, hi = n - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    const int64_t b = uniform64(by_lane ? d[mid].lane_base : d[mid].tile_base);
-    if (b <= key) lo = mid; else hi = mid - 1;
-  }
-  return uniform(lo);
-}
-
-// Descriptor fields as wave-uniform values. Every lane loads the same
-// descriptor; saying so (readfirstlane) keeps all control flow that depends
-// on it uniform: the compiler then never splits a wave across the exits of the
-// persistent loops.
-NXD ImgDesc uniform_desc(const ImgDesc* __restrict__ p) {
-  ImgDesc D = *p;
-  D.px = (uint8_t*)uniform64((int64_t)D.px);
-  D.H = uniform(D.H);
-  D.W = uniform(D.W);
-  D.ph = uniform(D.ph);
-  D.pw = uniform(D.pw);
-  D.nlx = uniform(D.nlx);
-  D.nly = uniform(D.nly);
-  D.lane_base = uniform64(D.lane_base);
-  D.px_base = uniform64(D.px_base);
-  D.tile_base = uniform64(D.tile_base);
-  D.ntx = uniform(D.ntx);
-  D.slot_base = uniform64(D.slot_base);
-  D.seed = (uint64_t)uniform64((int64_t)D.seed);
-  return D;
-}
-
-NXD uint32_t uniform_u(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
-
-// the whole workgroup (any block size) copies the weight image into LDS
-NXD void load_weights(float* lds, const float* __restrict__ w, int64_t nfloats) {
-  const int64_t n4 = nfloats >> 2;
-  for (int64_t i = threadIdx.x; i < n4; i += blockDim.x) ((float4*)lds)[i] = ((const float4*)w)[i];
-  __syncthreads();
-}
 
 // ------------------------------------------------------------------ full-image pass
 template <int H_, int C_>
@@ -358,45 +294,6 @@ __global__ void __launch_bounds__(256) k_rans_scatter(RansEncArgs A) {
       }
     }
   }
-}
-
-// Spread slots. A push of symbol (s, f) from a state x < f (only near the
-// start of a stream) takes the x-th (from 0) slot y of [0, 2^16) whose 16-bit
-// reversal lies in [s, s + f): reversal deals the range out about 2^16 / f
-// apart, so the state grows by about the symbol's probability, where the
-// usual rule would jump to s + x. The decoder recognises such a state (it is
-// below 2^16), searches the symbol with the reversed slot and pops by the
-// rank of y among the symbol's slots. Both walk the reversal's 16 bits from
-// the lowest: the range values with low bits r (j of them) and bit j clear
-// number floor((s + f - 1 - r) / 2^(j+1)) - floor((s - 1 - r) / 2^(j+1))
-// (the floors are arithmetic shifts).
-NXD uint32_t rev16(uint32_t v) { return __builtin_bitreverse32(v) >> 16; }
-
-NXD int32_t spread_count(int32_t lo, int32_t hi, int32_t r, int sh) { return ((hi - r) >> sh) - ((lo - r) >> sh); }
-
-NXD uint32_t spread_select(uint32_t x, uint32_t s, uint32_t f) {
-  const int32_t lo = (int32_t)s - 1, hi = (int32_t)(s + f) - 1;
-  int32_t r = 0, left = (int32_t)x;
-#pragma unroll
-  for (int j = 0; j < 16; ++j) {
-    const int32_t n0 = spread_count(lo, hi, r, j + 1);
-    const bool one = left >= n0;
-    left -= one ? n0 : 0;
-    r |= one ? (1 << j) : 0;
-  }
-  return rev16((uint32_t)r);
-}
-
-NXD uint32_t spread_rank(uint32_t y, uint32_t s, uint32_t f) {
-  const uint32_t v = rev16(y);
-  const int32_t lo = (int32_t)s - 1, hi = (int32_t)(s + f) - 1;
-  int32_t n = 0;
-#pragma unroll
-  for (int j = 0; j < 16; ++j) {
-    const int32_t r = (int32_t)(v & ((1u << j) - 1u));
-    n += ((v >> j) & 1u) ? spread_count(lo, hi, r, j + 1) : 0;
-  }
-  return (uint32_t)n;
 }
 
 // A push on a state x >= f first sheds low bytes while the state is at least
@@ -779,61 +676,12 @@ __global__ void __launch_bounds__(64) k_pack(PackArgs A) {
 }
 
 // ------------------------------------------------------------------ decoder
-// Bytes of the lane payload, staged 256 at a time: lane l of the wave holds
-// bytes base + 4l .. base + 4l + 3; a byte is fetched with a lane read.
-struct ByteStage {
-  const uint8_t* S;
-  uint32_t len, base;
-  uint32_t word;
-  NXD void fill(uint32_t at, int lane) {
-    // clamped, unconditional loads; bytes past the end read as 0
-    base = at;
-    const gbytes g = as_global(S);
-    uint32_t v = 0;
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      const uint32_t o = at + 4 * (uint32_t)lane + b;
-      const uint32_t byte = g[o < len ? o : len - 1];
-      v |= (o < len ? byte : 0u) << (8 * b);
-    }
-    word = v;
-  }
-  // byte at pos, pos >= base; the caller keeps pos < base + 256 (bytes past
-  // the window read as garbage, never as an out-of-range lane)
-  NXD uint32_t byte_at(uint32_t pos) const {
-    const uint32_t off = pos - base;
-    const uint32_t v = (uint32_t)__builtin_amdgcn_readlane((int)word, (int)((off >> 2) & 63u));
-    return (v >> (8 * (off & 3u))) & 255u;
-  }
-  NXD uint32_t get(uint32_t pos, int lane) {
-    if (pos - base >= 256u) fill(pos, lane);
-    return byte_at(pos);
-  }
-  // rANS renormalisation after a pop: at most two bytes are read (the popped
-  // state is at least 2^7 while bytes remain), each only while x < L and
-  // bytes remain; no branch except the rare window refill
-  NXD void renorm(uint32_t& x, uint32_t& pos, int lane, bool act = true) {
-    if (pos + 2u > base + 256u && pos < len) fill(pos & ~3u, lane);
-    const uint32_t b0 = byte_at(pos), b1 = byte_at(pos + 1u);
-    const bool r0 = act && x < RANS_L && pos < len;
-    x = r0 ? ((x << 8) | b0) : x;
-    pos += r0 ? 1u : 0u;
-    const bool r1 = x < RANS_L && pos < len;
-    x = r1 ? ((x << 8) | b1) : x;
-    pos += r1 ? 1u : 0u;
-  }
-};
-
 // ------------------------------------------------------------------ four-row decoding
 // With four streams per lane, the wave's 16-lane rows work independently:
 // row g searches the symbol of stream g while every lane evaluates all ten
 // mixture components at its own point, so no cross-row reduction is needed.
 // A pixel's mixture for the channel is staged in LDS as (w, a, b) of
 // component m at floats 3m..3m+2 of the pixel's row of the table.
-struct Mix10 {
-  float w[10], a[10], b[10];
-};
-
 NXD void load_mix10(Mix10& P, const float* prm, int pix) {
   const float4* s = (const float4*)(prm + pix * PRM_STRIDE);
   float v[32];
@@ -848,31 +696,6 @@ NXD void load_mix10(Mix10& P, const float* prm, int pix) {
     P.a[m] = v[3 * m + 1];
     P.b[m] = v[3 * m + 2];
   }
-}
-
-// F at bin edge k over all ten components in this lane. The terms and the
-// additions are those of cdf_eval: per lane group g the sum
-// s_g = (t_g + t_{g+4}) + t_{g+8} (groups 2 and 3 add an exact zero), then
-// (s_0 + s_1) + (s_2 + s_3); so the value is bit-identical to the encoder's.
-NXD float cdf_eval10(int k, const Mix10& P) {
-  const float e = bin_edge(k);
-  float t[10];
-#pragma unroll
-  for (int m = 0; m < 10; ++m) {
-    const float x = __builtin_amdgcn_exp2f(__builtin_fmaf(-e, P.a[m], P.b[m]));
-    t[m] = P.w[m] * __builtin_amdgcn_rcpf(1.0f + x);
-  }
-  const float s0 = (t[0] + t[4]) + t[8];
-  const float s1 = (t[1] + t[5]) + t[9];
-  const float s2 = t[2] + t[6];
-  const float s3 = t[3] + t[7];
-  return (s0 + s1) + (s2 + s3);
-}
-
-// bits of row g in a wave-wide ballot, counted
-NXD int row_count(uint64_t bal, int g) {
-  const uint32_t half = (g & 2) ? (uint32_t)(bal >> 32) : (uint32_t)bal;
-  return __builtin_popcount((half >> ((g & 1) << 4)) & 0xffffu);
 }
 
 // One stream per row: state, position and a 64-byte window of its bytes,
@@ -915,14 +738,6 @@ struct RowStream {
     x = r1 ? ((x << 8) | b1) : x;
     pos += r1 ? 1u : 0u;
   }
-};
-
-// K >= 8: one stream per pixel row of a 16-row group (K = 16), or one per
-// pair of rows p and p + 8 (K = 8); lane (p, g) holds stream p mod K's state,
-// the same in every lane of the pixel (and, for K = 8, of both rows)
-struct PixStream {
-  gbytes S;
-  uint32_t len, pos, x;
 };
 
 // One symbol of every pixel of a 16-row group, each from the pixel's own
@@ -969,67 +784,6 @@ NXD int pop_own(const Chan& Q, PixStream& P, bool act, uint32_t& start, uint32_t
   P.x = act ? xn : P.x;
   P.pos = act ? pn : P.pos;
   return lo;
-}
-
-// pop_own for the 16-lanes-per-pixel layout of the row decoder. A wave has
-// its SIMD to itself here, so the search trades instructions for a shorter
-// dependent chain: four quarterings of [0, 256) instead of eight halvings,
-// the three quartile points of a step evaluated together (cdf_eval16,
-// bitwise the encoder's CDF values; the CDF is increasing, so the points at
-// or below the slot are a prefix). The bracket found, and its CDF values,
-// are the bisection's.
-NXD int pop16(const Chan16& Q, PixStream& P, bool act, uint32_t& start, uint32_t& freq) {
-  const uint32_t lm = P.len - 1u;
-  const uint32_t nb0 = P.S[min(P.pos, lm)];
-  const uint32_t nb1 = P.S[min(P.pos + 1u, lm)];
-  const bool small = P.x < CDF_TOTAL;
-  const uint32_t slot = small ? rev16(P.x) : (P.x & 0xffffu);
-  int lo = 0;
-  uint32_t clo = 0u, chi = CDF_TOTAL;
-#pragma unroll
-  for (int st = 0; st < 4; ++st) {
-    const int d = 64 >> (2 * st);
-    const int k1 = lo + d, k2 = lo + 2 * d, k3 = lo + 3 * d;
-    const uint32_t v1 = cdf_quant(k1, cdf_eval16(k1, Q));
-    const uint32_t v2 = cdf_quant(k2, cdf_eval16(k2, Q));
-    const uint32_t v3 = cdf_quant(k3, cdf_eval16(k3, Q));
-    const bool l1 = v1 <= slot, l2 = v2 <= slot, l3 = v3 <= slot;
-    lo = l3 ? k3 : (l2 ? k2 : (l1 ? k1 : lo));
-    clo = l3 ? v3 : (l2 ? v2 : (l1 ? v1 : clo));
-    chi = l3 ? chi : (l2 ? v3 : (l1 ? v2 : v1));
-  }
-  freq = chi - clo;
-  start = clo;
-  uint32_t xn = freq * (P.x >> 16) + slot - clo;
-  if (__ballot(small && act) != 0ull) {
-    const uint32_t xr = spread_rank(P.x, clo, freq);
-    xn = small ? xr : xn;
-  }
-  uint32_t pn = P.pos;
-  const bool r0 = xn < RANS_L && pn < P.len;
-  xn = r0 ? ((xn << 8) | nb0) : xn;
-  pn += r0 ? 1u : 0u;
-  const bool r1 = xn < RANS_L && pn < P.len;
-  xn = r1 ? ((xn << 8) | nb1) : xn;
-  pn += r1 ? 1u : 0u;
-  P.x = act ? xn : P.x;
-  P.pos = act ? pn : P.pos;
-  return lo;
-}
-
-// a stream's initial state: its first bytes, most significant first, read
-// while x < L (at most four; loads clamped into the stream, len >= 1)
-NXD void stream_begin(PixStream& P) {
-  uint32_t xs = 0u, ps = 0u;
-#pragma unroll
-  for (int b = 0; b < 4; ++b) {
-    const uint32_t byte = P.S[min((uint32_t)b, P.len - 1u)];
-    const bool rd = xs < RANS_L && ps < P.len;
-    xs = rd ? ((xs << 8) | byte) : xs;
-    ps += rd ? 1u : 0u;
-  }
-  P.x = xs;
-  P.pos = ps;
 }
 
 // K: rANS streams of the lane; the chain pops K symbols (rows ts + q0 + k,
@@ -1499,231 +1253,6 @@ __global__ void __launch_bounds__(NWAVES_DEC * 64) k_decode(DecArgs A) {
   }
 }
 
-// ------------------------------------------------------------------ row streams
-// Row streams (one rANS stream per lane row): a lane is decoded in bands of
-// ROW_BAND = 16 rows, one workgroup of ROW_WAVES = 4 waves (one per SIMD) per
-// band, so one wavefront step of a band, up to 16 pixels, is shared by a whole
-// CU: the network is split by output tiles (net_forward_split, activations
-// exchanged through LDS), then each wave decodes four of the band's rows with
-// 16 lanes per pixel, one mixture component per lane. Each row pops its own
-// stream, so every row of a step decodes at once (the whole step of
-// Algorithm 1 in parallel); a row's coder state stays in the registers of
-// the lanes that decode it. A band's top rows read the h rows above, decoded
-// by the band above it, possibly on another CU: each band publishes how many
-// steps it has finished (release), and waits before step t until the band
-// above has finished step t - 1 (acquire). Bands are taken from the queue in
-// order (by the step they start at, across the images of the batch), so the
-// band above is always held by a running or finished workgroup; its skew of
-// (h + 1) ROW_BAND steps makes waits rare once a band has started. A wait also
-// ends, with the image marked corrupt, if it exceeds band_wait_ticks of the
-// 100 MHz clock (20 s unless a test lowers it), so every workgroup reaches
-// the end of the kernel whatever happens.
-constexpr int32_t BAND_DONE = 0x7fffffff;
-
-NXD int find_img_band(const ImgDesc* __restrict__ d, int n, int64_t key) {
-  int lo = 0, hi = n - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    const int64_t b = uniform64(d[mid].band_base);
-    if (b <= key) lo = mid; else hi = mid - 1;
-  }
-  return uniform(lo);
-}
-
-NXD void band_publish(int32_t* slot, int32_t v) {
-  __hip_atomic_store(slot, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-template <int H_, int C_, bool TRACE>
-__device__ void decode_band(const DecArgs& A, const float* w, float* xb, float* hb, float* cb, int32_t* sh,
-                            int64_t B) {
-  static_assert(ROW_BAND == 16 && ROW_WAVES == 4, "a band is one 16-pixel tile, four rows per wave");
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int p = lane & 15;                 // network phase: the tile's pixel p is band row p
-  const int m = lane & 15, pp = 4 * wave + (lane >> 4);  // mixture phase: component m of band row pp
-  const int n = find_img_band(A.desc, A.n_img, B);
-  const ImgDesc D = uniform_desc(A.desc + n);
-  // which lane of the image and which band of it: lanes in order, full patch
-  // rows first, each lane cut into bands_of(Hl) bands
-  const int64_t bi = B - D.band_base;
-  const int64_t per_prow = (int64_t)D.nlx * bands_of(D.ph);
-  const int ly = (int)(bi / per_prow);
-  const int y0 = ly * D.ph, Hl = min(D.ph, D.H - y0);
-  const int64_t rem = bi - (int64_t)ly * per_prow;
-  const int lx = (int)(rem / bands_of(Hl)), bb = (int)(rem - (int64_t)lx * bands_of(Hl));
-  const int x0 = lx * D.pw, Wl = min(D.pw, D.W - x0);
-  const int nl = D.nlx * D.nly;
-  const int r0 = bb * ROW_BAND, r1 = min(Hl, r0 + ROW_BAND) - 1, nrows = r1 - r0 + 1;
-  int32_t* mine = A.progress + B;
-  // header and stream table (every lane reads the same bytes)
-  const uint8_t* C = A.in + uniform64((int64_t)A.in_off[n]);
-  const int64_t clen = uniform64((int64_t)(A.in_off[n + 1] - A.in_off[n]));
-  const int64_t ns = image_streams(ROW_STREAMS, D.H, D.nlx, D.nly);
-  const int64_t pay = HDR_BYTES + 4 * ns;
-  bool ok = clen >= pay;
-  bool mismatch = false;
-  if (ok) {
-    const uint32_t ph = D.ph == D.H ? 0u : (uint32_t)D.ph, pw = D.pw == D.W ? 0u : (uint32_t)D.pw;
-    ok = C[0] == 'N' && C[1] == 'L' && C[2] == 'X' && C[3] == 'C' && C[4] == CONTAINER_VERSION && C[5] == 1 &&
-         C[6] == (uint8_t)H_ && C[7] == (uint8_t)ROW_STREAMS && rd_u32(C + 8) == (uint32_t)D.H &&
-         rd_u32(C + 12) == (uint32_t)D.W && (uint32_t)(C[16] | (C[17] << 8)) == ph &&
-         (uint32_t)(C[18] | (C[19] << 8)) == pw && rd_u32(C + 28) == (uint32_t)nl;
-    ok = ok && pay + (int64_t)rd_u32(C + HDR_BYTES + 4 * (ns - 1)) == clen;
-    ok = uniform(ok ? 1 : 0) != 0;
-    if (ok) {
-      const uint64_t hsh = (uint64_t)rd_u32(C + 20) | ((uint64_t)rd_u32(C + 24) << 32);
-      mismatch = uniform(hsh != A.model_hash ? 1 : 0) != 0;
-    }
-  }
-  // this lane's row stream (band row pp; rows past the band's last take the
-  // last row's and never pop), in every lane of the row's pixel
-  const int64_t ebase = row_entry_base(ly, lx, D.nlx, D.ph, Hl) + r0;
-  if (threadIdx.x == 0) sh[0] = 1;
-  __syncthreads();
-  PixStream P;
-  P.x = 0u;
-  P.pos = 0u;
-  P.len = 1u;
-  P.S = as_global(C);
-  if (ok && !mismatch) {
-    const int64_t e = ebase + min(pp, nrows - 1);
-    const uint32_t lend = rd_u32(C + HDR_BYTES + 4 * e);
-    const uint32_t lstart = e > 0 ? rd_u32(C + HDR_BYTES + 4 * (e - 1)) : 0u;
-    const bool okr = lstart <= lend && pay + (int64_t)lend <= clen && lend - lstart >= 1;
-    if (okr) {
-      P.S = as_global(C + pay + lstart);
-      P.len = lend - lstart;
-      stream_begin(P);
-    } else {
-      sh[0] = 0;
-    }
-  }
-  __syncthreads();
-  ok = ok && sh[0] != 0;
-  if (mismatch || !ok) {
-    if (threadIdx.x == 0) {
-      A.status[n] = mismatch ? ST_MISMATCH : ST_CORRUPT;
-      band_publish(mine, BAND_DONE);  // the band below must not wait for this one
-    }
-    __syncthreads();
-    return;
-  }
-  uint8_t* img = D.px;
-  const int o = H_ + 1;
-  const int t_lo = o * r0, t_hi = (Wl - 1) + o * r1;
-  uint32_t* dump = TRACE ? A.sym_dump + D.px_base * 3 : nullptr;
-  int32_t seen = bb == 0 ? BAND_DONE : 0;  // steps of the band above known to be finished
-  for (int t = t_lo; t <= t_hi; ++t) {
-    if (seen < t) {
-      // wait until the band above has finished step t - 1
-      if (threadIdx.x == 0) {
-        const int32_t* above = A.progress + (B - 1);
-        int32_t v = __hip_atomic_load(above, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
-        if (v < t) {
-          const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
-          while (v < t) {
-            __builtin_amdgcn_s_sleep(4);
-            v = __hip_atomic_load(above, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
-            if (v < t && __builtin_amdgcn_s_memrealtime() - t0 > A.band_wait_ticks) {
-              A.status[n] = ST_CORRUPT;  // never expected: the image cannot be trusted
-              v = BAND_DONE;
-            }
-          }
-        }
-        sh[1] = v;
-      }
-      __syncthreads();
-      seen = sh[1];
-    }
-    // this band's step t - 1 is finished in every wave (its pixels stored)
-    __syncthreads();
-    if (threadIdx.x == 0) band_publish(mine, t);
-    int ilo, ihi;
-    step_rows(t, Hl, Wl, o, ilo, ihi);
-    const int a = max(ilo, r0), bmax = min(ihi, r1);
-    if (a > bmax) continue;  // the same for the whole workgroup
-    // network: the waves gather a share of the tile's contexts each, then
-    // compute their share of the layers
-    {
-      const int i = r0 + p;
-      const bool active = i >= a && i <= bmax;
-      float ctx[conv_chunks(H_)];
-      gather_shared<H_, ROW_WAVES>(ctx, img, D.W, y0, x0, Hl, Wl, i, t - o * i, active, wave, cb, lane);
-      net_forward_split<H_, C_, ROW_WAVES>(lds_weights(w), A.nb, ctx, xb, hb, lane, wave);
-    }
-    // mixture and pops: band row pp, component m
-    const int i = r0 + pp;
-    const bool act = i >= a && i <= bmax;
-    const int j = t - o * i;
-    const bool live = m < 10;
-    Mix16 M;
-    mix_prep16(hb + pp * 128, m, M);
-    int xv[3] = {0, 0, 0};
-    float xr = 0.0f, xg = 0.0f;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      Chan16 Q;
-      chan_params16(M, c, xr, xg, Q);
-      uint32_t start, freq;
-      const int sy = pop16(Q, P, act, start, freq);
-      if (c == 0) xv[0] = sy;
-      else if (c == 1) xv[1] = sy;
-      else xv[2] = sy;
-      if (TRACE && act && m == 0)
-        dump[((int64_t)(y0 + i) * D.W + (x0 + j)) * 3 + c] = start | (freq << 16);
-      if (c == 0) {
-        posterior16(M, xv[0], Q, live);
-        xr = normalise(xv[0]);
-      } else if (c == 1) {
-        posterior16(M, xv[1], Q, live);
-        xg = normalise(xv[1]);
-      }
-    }
-    if (act && m == 0) {
-      uint8_t* dst = img + ((int64_t)(y0 + i) * D.W + (x0 + j)) * 3;
-      dst[0] = (uint8_t)xv[0];
-      dst[1] = (uint8_t)xv[1];
-      dst[2] = (uint8_t)xv[2];
-    }
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) band_publish(mine, BAND_DONE);
-  // every row's stream must end in the start state with every byte read
-  if (pp < nrows && m == 0 && !(P.x == RANS_X0 && P.pos == P.len)) A.status[n] = ST_CORRUPT;
-  __syncthreads();
-}
-
-// LDS of the row decoder after the weights: two activation exchange buffers
-// of C/16 tiles, the band's 16 x 128 head rows, the tile's contexts (64 lanes
-// x gather_stride), then a few shared words
-template <int H_, int C_>
-constexpr size_t rows_lds_extra() {
-  return (size_t)(2 * (C_ / 16) * 256 + ROW_BAND * 128 + 64 * gather_stride<H_>()) * sizeof(float) +
-         4 * sizeof(int32_t);
-}
-
-template <int H_, int C_, bool TRACE>
-__global__ void __launch_bounds__(ROW_WAVES * 64) k_decode_rows(DecArgs A) {
-  extern __shared__ float4 smem_f4[];
-  float* w = (float*)smem_f4;
-  load_weights(w, A.w, A.wfloats);
-  float* xb = w + A.wfloats;
-  float* hb = xb + 2 * (C_ / 16) * 256;
-  float* cb = hb + ROW_BAND * 128;
-  int32_t* sh = (int32_t*)(cb + 64 * gather_stride<H_>());  // band, wait and flag words shared by the workgroup
-  for (;;) {
-    if (threadIdx.x == 0) sh[2] = atomicAdd(A.counter, 1);
-    __syncthreads();
-    const int64_t Q = sh[2];
-    __syncthreads();
-    if (Q >= A.n_bands) break;
-    // the queue's order of the bands (start step, then image and lane), or image order
-    const int64_t B = A.band_order ? (int64_t)uniform(A.band_order[Q]) : Q;
-    if (B < 0 || B >= A.n_bands) continue;  // only a damaged workspace: never decode out of range
-    decode_band<H_, C_, TRACE>(A, w, xb, hb, cb, sh, B);
-  }
-}
-
 __global__ void k_decode_prep(int32_t* status, int n_img, int32_t* counter, int32_t* progress, int64_t n_bands) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (status && i < n_img) status[i] = ST_OK;
@@ -1818,14 +1347,6 @@ bool supported(int h, int C) {
          (h == 1 && (C == 16 || C == 32));
 }
 
-// kernels keep the whole weight image in LDS: allow up to the device limit
-template <typename K>
-static hipError_t allow_lds(K kernel, size_t lds) {
-  const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (e != hipSuccess) (void)hipGetLastError();  // reported here, not by the next launch's check
-  return e;
-}
-
 template <int H_, int C_>
 static hipError_t pass_t(const PassArgs& a, int grid, hipStream_t s) {
   const size_t lds = (size_t)a.wfloats * 4;
@@ -1864,14 +1385,6 @@ static hipError_t decode_setup_k() {
 
 template <int H_, int C_>
 static hipError_t decode_setup(int K) {
-  if (K == ROW_STREAMS) {
-    int dev = 0, lim = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e == hipSuccess) e = hipDeviceGetAttribute(&lim, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
-    if (e == hipSuccess) e = allow_lds(k_decode_rows<H_, C_, false>, (size_t)lim);
-    if (e == hipSuccess) e = allow_lds(k_decode_rows<H_, C_, true>, (size_t)lim);
-    return e;
-  }
   if (K == 2) return decode_setup_k<H_, C_, 2>();
   if (K == 4) return decode_setup_k<H_, C_, 4>();
   if (K == 8) return decode_setup_k<H_, C_, 8>();
@@ -1897,19 +1410,6 @@ static hipError_t decode_t(const DecArgs& a, int grid, int waves, hipStream_t s)
   if (a.K == 16) return decode_k<H_, C_, 16>(a, grid, waves, s);
   return decode_k<H_, C_, 1>(a, grid, waves, s);
 }
-
-#define NX_DISPATCH(FN, h, C, ...)                          \
-  do {                                                      \
-    if (h == 3 && C == 64) return FN<3, 64>(__VA_ARGS__);   \
-    if (h == 3 && C == 32) return FN<3, 32>(__VA_ARGS__);   \
-    if (h == 3 && C == 16) return FN<3, 16>(__VA_ARGS__);   \
-    if (h == 2 && C == 64) return FN<2, 64>(__VA_ARGS__);   \
-    if (h == 2 && C == 32) return FN<2, 32>(__VA_ARGS__);   \
-    if (h == 2 && C == 16) return FN<2, 16>(__VA_ARGS__);   \
-    if (h == 1 && C == 32) return FN<1, 32>(__VA_ARGS__);   \
-    if (h == 1 && C == 16) return FN<1, 16>(__VA_ARGS__);   \
-    return hipErrorInvalidValue;                            \
-  } while (0)
 
 hipError_t launch_pass(int h, int C, const PassArgs& a, int grid, hipStream_t s) {
   if (a.n_tiles == 0) return hipSuccess;
@@ -1994,21 +1494,6 @@ hipError_t launch_decode_prep(int32_t* status, int n_img, int32_t* counter, hipS
   hipLaunchKernelGGL(k_decode_prep, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, s, status, n_img, counter,
                      progress, n_bands);
   return hipGetLastError();
-}
-
-template <int H_, int C_>
-static hipError_t rows_t(const DecArgs& a, int grid, hipStream_t s) {
-  const size_t lds = (size_t)a.wfloats * 4 + rows_lds_extra<H_, C_>();
-  if (a.sym_dump)
-    hipLaunchKernelGGL((k_decode_rows<H_, C_, true>), dim3(grid), dim3(ROW_WAVES * 64), lds, s, a);
-  else
-    hipLaunchKernelGGL((k_decode_rows<H_, C_, false>), dim3(grid), dim3(ROW_WAVES * 64), lds, s, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_decode_rows(int h, int C, const DecArgs& a, int grid, hipStream_t s) {
-  if (a.n_bands == 0) return hipSuccess;
-  NX_DISPATCH(rows_t, h, C, a, grid, s);
 }
 
 hipError_t launch_reduce_bits(const ImgDesc* desc, int n_img, const float* bits, double* partials, double* out,

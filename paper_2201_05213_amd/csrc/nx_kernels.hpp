@@ -94,6 +94,7 @@ struct DecArgs {
   uint32_t* sym_dump;      // nullable: (start | freq << 16) used per pixel/channel
   uint8_t* ring;           // order 2: grid x waves context rings of ring_wave_bytes(ring_rows)
   int ring_rows;
+  int team_rows;           // teams: rows of a team's context window in LDS
   int32_t* progress;       // row streams: per band, the steps it has finished (zeroed by the prep)
   int64_t n_bands;         // row streams: bands of the batch (the queue's work items)
   uint64_t band_wait_ticks;  // row streams: the longest wait on the band above (100 MHz clock ticks)
@@ -167,6 +168,18 @@ hipError_t launch_decode_prep(int32_t* status, int n_img, int32_t* counter, hipS
 // row streams: the band decoder (four waves per workgroup, one per SIMD, one band at a time)
 constexpr int ROW_WAVES = 4;
 hipError_t launch_decode_rows(int h, int C, const DecArgs& a, int grid, hipStream_t s);
+// Few lanes: teams of four waves per lane (nx_team.hip), `teams` lanes a
+// workgroup and CU. decode_teams: how many, or 0 for the wave-per-lane
+// decoder (launch_decode, launch_sample). A lone wave issues a group of 16
+// pixels in 26 to 32 thousand cycles, a team in 15 to 18; two teams share their SIMDs'
+// issue (27 thousand for a group of each) and still beat two lone waves on two
+// SIMDs (36); three or four would not. So
+// the line is at two lanes per CU, in either wavefront layout, where `rows`
+// (window rows of the tallest lane) fit the LDS left by the weights.
+int decode_teams(int h, int C, int64_t wfloats, int64_t n_lanes, int order, int64_t rows, int cus, size_t lds);
+hipError_t launch_decode_team(int h, int C, const DecArgs& a, int teams, bool sample, hipStream_t s);
+// raise the LDS limit of the team kernels, or of the row-stream decoder's
+hipError_t prepare_team(int h, int C, bool rows);
 // raise the decoder kernels' LDS limit (once, outside any stream capture)
 hipError_t prepare_decode(int h, int C, int K);
 // waves per workgroup in 1..DECODE_WAVES (the LDS takes one pivot table per wave);
