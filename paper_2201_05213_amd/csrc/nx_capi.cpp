@@ -418,8 +418,7 @@ TrainArgs train_args(const TrainPlan& T, const uint8_t* imgs, uint8_t* ws, const
 }
 
 int train_grid(const TrainPlan& T) {
-  const int64_t need = (T.ntiles + 15) / 16;
-  return (int)std::max<int64_t>(1, std::min<int64_t>(need, device_cus()));
+  return (int)std::max<int64_t>(1, std::min<int64_t>(T.ntiles, device_cus()));
 }
 
 }  // namespace
