@@ -655,8 +655,8 @@ static nellox_status prepare_impl(nellox_model* m, int32_t n, const nellox_image
 }
 
 // lanes per CU decoded by teams of waves, 0: a wave per lane
-static int teams_of(const nellox_model* m, int64_t n_lanes, int order, int64_t rows) {
-  return decode_teams(m->h, m->Cp, m->wfloats, n_lanes, order, rows, m->num_cu, m->lds);
+static int teams_of(const nellox_model* m, int K, int64_t n_lanes, int order, int64_t rows) {
+  return decode_teams(K, m->wfloats, n_lanes, order, rows, m->num_cu, m->lds);
 }
 
 static nellox_status run_impl(nellox_model* m, const nellox_decode_plan* plan, const uint8_t* in,
@@ -706,9 +706,9 @@ static nellox_status run_impl(nellox_model* m, const nellox_decode_plan* plan, c
   if (rows) {
     a.K = ROW_STREAMS;
     e = launch_decode_rows(m->h, m->Cp, a, plan->grid, s);
-  } else if (const int teams = teams_of(m, plan->n_lanes, plan->order, plan->ring_rows)) {
+  } else if (const int teams = teams_of(m, plan->interleave, plan->n_lanes, plan->order, plan->ring_rows)) {
     a.team_rows = (int)plan->ring_rows;
-    e = launch_decode_team(m->h, m->Cp, a, teams, false, s);
+    e = launch_decode_team(m->h, m->Cp, a, teams, s);
   } else {
     e = launch_decode(m->h, m->Cp, a, plan->grid, plan->waves, s);
   }
@@ -794,7 +794,7 @@ nellox_status nellox_sample(const nellox_model* mc, int32_t n, const uint64_t* s
   hipStream_t s = (hipStream_t)stream;
   uint8_t* w8 = (uint8_t*)ws;
   const int64_t rows = ring_rows_for(P.ph_max, m->h);
-  const int teams = teams_of(m, P.n_lanes, o->order, rows);
+  const int teams = teams_of(m, 0, P.n_lanes, o->order, rows);
   hipError_t e = teams ? prepare_team(m->h, m->Cp, false) : prepare_decode(m->h, m->Cp, 4);
   if (e != hipSuccess) return hip_fail(e, "sampler set-up");
   if ((st = upload_plan(m, P, w8, W, s))) return st;
@@ -809,7 +809,7 @@ nellox_status nellox_sample(const nellox_model* mc, int32_t n, const uint64_t* s
   a.n_img = n;
   a.n_lanes = P.n_lanes;
   a.order = o->order;
-  a.K = 4;
+  a.K = teams ? 0 : 4;
   a.model_hash = m->hash;
   a.counter = counter;
   a.ring = o->order == 2 ? w8 + W.ring : nullptr;
@@ -817,7 +817,7 @@ nellox_status nellox_sample(const nellox_model* mc, int32_t n, const uint64_t* s
   int grid = 0, waves = 0;
   decode_shape(P.n_lanes, persistent_grid(m), grid, waves);
   a.team_rows = (int)rows;
-  e = teams ? launch_decode_team(m->h, m->Cp, a, teams, true, s) : launch_sample(m->h, m->Cp, a, grid, waves, s);
+  e = teams ? launch_decode_team(m->h, m->Cp, a, teams, s) : launch_sample(m->h, m->Cp, a, grid, waves, s);
   if (e != hipSuccess) return hip_fail(e, "sampler launch");
   return NELLOX_OK;
 }

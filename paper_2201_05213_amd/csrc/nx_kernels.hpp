@@ -165,19 +165,20 @@ hipError_t launch_rans_encode(const RansEncArgs& a, hipStream_t s);
 hipError_t launch_pack(const PackArgs& a, hipStream_t s);
 hipError_t launch_decode_prep(int32_t* status, int n_img, int32_t* counter, hipStream_t s,
                               int32_t* progress = nullptr, int64_t n_bands = 0);
-// row streams: the band decoder (four waves per workgroup, one per SIMD, one band at a time)
+// row streams: the band decoder (a team of four waves, and one more, per workgroup, one band at a time)
 constexpr int ROW_WAVES = 4;
 hipError_t launch_decode_rows(int h, int C, const DecArgs& a, int grid, hipStream_t s);
 // Few lanes: teams of four waves per lane (nx_team.hip), `teams` lanes a
 // workgroup and CU. decode_teams: how many, or 0 for the wave-per-lane
 // decoder (launch_decode, launch_sample). A lone wave issues a group of 16
-// pixels in 26 to 32 thousand cycles, a team in 15 to 18; two teams share their SIMDs'
-// issue (27 thousand for a group of each) and still beat two lone waves on two
-// SIMDs (36); three or four would not. So
-// the line is at two lanes per CU, in either wavefront layout, where `rows`
-// (window rows of the tallest lane) fit the LDS left by the weights.
-int decode_teams(int h, int C, int64_t wfloats, int64_t n_lanes, int order, int64_t rows, int cus, size_t lds);
-hipError_t launch_decode_team(int h, int C, const DecArgs& a, int teams, bool sample, hipStream_t s);
+// pixels in 26 to 32 thousand cycles (model B), a team in 14 to 17; two teams
+// share their SIMDs' issue (20 thousand for a group of each, 512 thumbnails) and still
+// beat two lone waves (36); three or four would not. So the line is at two lanes per
+// CU, in either wavefront layout, where `rows` (window rows of the tallest
+// lane) fit the LDS left by the weights.
+// K: rANS streams per lane, 0 to sample (also DecArgs.K of the launch).
+int decode_teams(int K, int64_t wfloats, int64_t n_lanes, int order, int64_t rows, int cus, size_t lds);
+hipError_t launch_decode_team(int h, int C, const DecArgs& a, int teams, hipStream_t s);
 // raise the LDS limit of the team kernels, or of the row-stream decoder's
 hipError_t prepare_team(int h, int C, bool rows);
 // raise the decoder kernels' LDS limit (once, outside any stream capture)

@@ -5,12 +5,11 @@
 // A wave that decodes a lane alone spends 26 to 32 thousand cycles on a group
 // of 16 pixels, most of them issuing instructions, while the other SIMDs of its CU
 // idle if there is at most one lane per CU (or two). A team shares the group:
-//   network     wave w computes the output tiles mt = w (mod 4) of each layer
-//               and head tiles w and w + 4; activations are exchanged
-//               through LDS, the head rows go to a 16 x 128 table there
-//               (net_team)
-//   mixture     wave w decodes four of the group's pixels with 16 lanes per
-//               pixel, lane m holding component m
+// a wave takes four of its pixels, from their contexts to their symbols, and the
+// team meets once per group, when the context window has the new pixels.
+//   network     on v_mfma_f32_4x4x1f32 (16 blocks), four pixels by 64
+//               outputs an instruction (net_quad)
+//   mixture     16 lanes per pixel, lane m holding component m
 // Every value is computed by the operations, in the order, of the other
 // decoders and of the encoder: bitwise theirs.
 #include <hip/hip_runtime.h>
@@ -31,20 +30,30 @@ namespace nx {
 // follow each other without a wrap.
 constexpr int WIN_PLANES = 2 * 3 * RING_COLS;
 
+// Pixel r = lane % 4 of a wave's four, block a = lane / 4: value j of the lane
+// is input k = 16 j + a of the pixel. What its place in the window has besides
+// the step and the pixel's row is the lane's for good.
 template <int H_>
-NXD void gather_lds(float (&ctx)[conv_chunks(H_)], const int16_t* win, int rows, int t, int i, int lane) {
-  constexpr int Q = H_ * (H_ + 2), R = 3 * (2 * H_ + 1);
-  const int g = lane >> 4;
-  const int16_t* b = win + (3 * ((t - Q) & (RING_COLS - 1)) + g) * rows + i;
-  int raw[conv_chunks(H_)];
+constexpr int quad_inputs() { return (4 * conv_chunks(H_) + 15) / 16; }
+template <int H_>
+NXD void quad_offsets(int (&off)[quad_inputs<H_>()], int rows, int lane) {
 #pragma unroll
-  for (int kc = 0; kc < conv_chunks(H_); ++kc) {
-    const int d0 = (4 * kc / R) < H_ ? 4 * kc / R : H_, d1 = ((4 * kc + 3) / R) < H_ ? (4 * kc + 3) / R : H_;
-    const int o0 = (4 * kc - 3 * H_ * d0) * rows + d0, o1 = (4 * kc - 3 * H_ * d1) * rows + d1;
-    raw[kc] = b[d0 == d1 ? o0 : (4 * kc + g >= R * d1 ? o1 : o0)];
+  for (int j = 0; j < quad_inputs<H_>(); ++j) {
+    const int k = min(16 * j + (lane >> 2), 4 * conv_chunks(H_) - 1);
+    const int dy = min(k / (3 * (2 * H_ + 1)), H_);
+    off[j] = (k - 3 * H_ * dy) * rows + dy;
   }
+}
+// contexts of the wave's pixels at step t, i the window row of the lane's
+template <int H_>
+NXD void quad_gather(float (&cx)[quad_inputs<H_>()], const int (&off)[quad_inputs<H_>()], const int16_t* win, int rows,
+                     int t, int i) {
+  const int16_t* b = win + 3 * ((t - H_ * (H_ + 2)) & (RING_COLS - 1)) * rows + i;
+  int raw[quad_inputs<H_>()];
 #pragma unroll
-  for (int kc = 0; kc < conv_chunks(H_); ++kc) ctx[kc] = (float)raw[kc] * (1.0f / 255.0f);
+  for (int j = 0; j < quad_inputs<H_>(); ++j) raw[j] = b[off[j]];
+#pragma unroll
+  for (int j = 0; j < quad_inputs<H_>(); ++j) cx[j] = (float)raw[j] * (1.0f / 255.0f);
 }
 
 // both copies of plane `plane` (of column t), row r
@@ -55,96 +64,141 @@ NXD void win_put(int16_t* win, int rows, int t, int ch, int r, int v) {
 }
 
 // ------------------------------------------------------------------ network
-// The network of one 16-pixel tile by the four waves of a team. xb: the
-// exchange buffer of C/16 tiles x 64 lanes x 4 floats; hb: the head table
-// [pixel][128] (permuted rows), whose start is the second exchange buffer (the
-// two are used in turn, and the last exchange, before the head rows are
-// written, is in xb). Each output element is the chain of MFMAs net_forward
-// computes for it, in the same k order. A layer's weights are read from LDS
-// before the barrier that makes its inputs readable. 2 nb + 2 barriers (of the
-// whole workgroup), the last making hb readable.
+// The network of a wave's four pixels. v_mfma_f32_4x4x1f32 adds 16 outer
+// products (blocks) of 4 x 4; with the activations as its A operand, one
+// block's four pixels broadcast to all (cbsz 4, block abid), and the weights
+// as B, it is one input k of 64 outputs: lane l has output l, register v pixel
+// v, and A's block abid has input k of pixel r in lane 4 abid + r. Inputs are
+// added in the order k = 0, 1, ..., the order, and with the roundings, of the
+// 16x16x4 form (each a chain of fused multiply-adds). A layer's outputs become the
+// next one's A operand by a 4 x 4 transpose within each four lanes. (C < 64:
+// the lanes past C repeat the others.) No value leaves the wave: split by
+// output tiles instead, a layer is 16 instructions of 32 cycles and not 64 of
+// 12.5 (each waits for the last), but six exchanges through LDS a group cost
+// 600 cycles each. Model B's network: 7.3 thousand cycles a group so split,
+// about 6 so; one 1024 x 1024 image with a stream per row, with the link wave below: 34.6 -> 29.9 ms.
+// Head row 64 i + l goes to hb[pixel * HB_STRIDE + 64 i + l].
 constexpr int TEAM_WAVES = ROW_WAVES;
+constexpr int HB_STRIDE = 132;
+template <int A>
+NXD f4 quad_mfma(float act, float w, f4 d) { return __builtin_amdgcn_mfma_f32_4x4x1f32(act, w, d, 4, A, 0); }
+
+template <int CTRL>
+NXD float quad_dpp(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+// x[j] of lane 4 a + r = u[r] of lane 4 a + j
+NXD f4 quad_transpose(const f4& u, int lane) {
+  const bool o0 = lane & 1, o1 = lane & 2;
+  // (all lanes exchange, then each picks: no branch around an exchange)
+  f4 e, y, x;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) e[c] = quad_dpp<0xB1>(u[c ^ 1]);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) y[c] = o0 == ((c & 1) != 0) ? u[c] : e[c];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) e[c] = quad_dpp<0x4E>(y[c ^ 2]);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) x[c] = o1 == ((c & 2) != 0) ? y[c] : e[c];
+  return x;
+}
+NXD f4 quad_act(const f4& a, int lane) {
+  f4 u;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) u[v] = xelu(a[v]);
+  return quad_transpose(u, lane);
+}
+NXD f4 splat(float b) { return f4{b, b, b, b}; }
+
+// The weights of 16 inputs, N outputs a lane (rows `stride` floats apart): four
+// 16-byte reads of LDS each. They are issued a chunk of 16 inputs ahead of
+// their use (the barrier to scheduling keeps them there): read where they are used, they cost
+// a wait of about 130 cycles in every chunk of 200.
+template <int N>
+struct QuadW {
+  f4 v[4][N];
+  NXD void load(const float* w, int stride) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+#pragma unroll
+      for (int n = 0; n < N; ++n) v[g][n] = *(const f4*)(w + n * stride + 64 * g);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+};
+// 16 inputs of block 4 CT's lanes on: chunk (ct, q) of the 16x16x4 form holds
+// inputs 16 ct + 4 g + q, g = 0 .. 3, and their order is the order here
+template <int CT, int N, int Q = 0, int G = 0>
+NXD void quad_chunk(const QuadW<N>& w, const f4& x, f4 (&d)[N]) {
+#pragma unroll
+  for (int n = 0; n < N; ++n) d[n] = quad_mfma<4 * CT + G>(x[Q], w.v[G][n][Q], d[n]);
+  if constexpr (G < 3) quad_chunk<CT, N, Q, G + 1>(w, x, d);
+  else if constexpr (Q < 3) quad_chunk<CT, N, Q + 1, 0>(w, x, d);
+}
+// a layer of 16 CTS inputs; w[0] holds its first chunk, and in the end what
+// `next` points at
+template <int CTS, int N, int CT = 0>
+NXD void quad_layer(const float* wl, int stride, const float* next, const f4& x, QuadW<N> (&w)[2], f4 (&d)[N]) {
+  w[(CT + 1) & 1].load(CT + 1 < CTS ? wl + (CT + 1) * 256 : next, stride);
+  quad_chunk<CT, N>(w[CT & 1], x, d);
+  if constexpr (CT + 1 < CTS) quad_layer<CTS, N, CT + 1>(wl, stride, next, x, w, d);
+  else if constexpr (CTS & 1) w[0] = w[1];
+}
+// inputs 16 kq .. of the first layer (there in ascending order)
+template <int H_, int KQ_, int Q = 0, int G = 0>
+NXD void quad_first_chunk(const QuadW<1>& w, float cx, f4& d) {
+  if constexpr (4 * KQ_ + Q < conv_chunks(H_)) {
+    d = quad_mfma<4 * Q + G>(cx, w.v[G][0][Q], d);
+    if constexpr (G < 3) quad_first_chunk<H_, KQ_, Q, G + 1>(w, cx, d);
+    else if constexpr (Q < 3) quad_first_chunk<H_, KQ_, Q + 1, 0>(w, cx, d);
+  }
+}
+template <int H_, int KQ_ = 0>
+NXD void quad_first(const float* wl, const float* next, const float (&cx)[quad_inputs<H_>()], QuadW<1> (&w)[2], f4& d) {
+  constexpr int KQ = conv_quads(H_), P = (KQ_ + KQ) & 1;  // the last chunk in w[1]
+  w[P ^ 1].load(KQ_ + 1 < KQ ? wl + (KQ_ + 1) * 256 : next, 0);
+  quad_first_chunk<H_, KQ_>(w[P], cx[KQ_], d);
+  if constexpr (KQ_ + 1 < KQ) quad_first<H_, KQ_ + 1>(wl, next, cx, w, d);
+}
+
 template <int H_, int C_>
-NXD void net_team(const float* __restrict__ w, int nb, const float (&ctx)[conv_chunks(H_)], float* xb, float* hb,
-                  int lane, int wv) {
+NXD void net_quad(const float* __restrict__ w, int nb, const float (&cx)[quad_inputs<H_>()], float* hb, int lane) {
   constexpr int MT = C_ / 16;
-  constexpr int KC = conv_chunks(H_), KQ = conv_quads(H_);
-  static_assert(MT <= TEAM_WAVES && HEAD_TILES == 2 * TEAM_WAVES, "a wave owns at most one tile, two of the head");
   const WeightLayout L = weight_layout(H_, C_, 0);
-  const int g = lane >> 4;
+  const int l = lane & (C_ - 1), r16 = lane & 15;
   const int layer_stride = MT * MT * 256;
   const float* bias_conv = w + L.head + HEAD_TILES * MT * 256 + 2 * nb * layer_stride;
   const float* bias_head = bias_conv + C_ + 2 * nb * C_;
-  const float* w_head = w + L.layer0 + 2 * nb * layer_stride;
-  const bool own = wv < MT;
-  const int mt = own ? wv : 0;
-
-  f4 a, z, wn[MT], bn;
-  auto load_tile = [&](const float* wl, int tile, f4(&q)[MT]) {
-#pragma unroll
-    for (int ct = 0; ct < MT; ++ct) q[ct] = *(const f4*)(wl + ((tile * MT + ct) * 64 + lane) * 4);
-  };
-  auto load_bias = [&](const float* b, int tile) { return *(const f4*)(b + 16 * tile + 4 * g); };
-  auto chain = [&](const f4(&q)[MT], const f4(&in)[MT], f4 acc) {
-#pragma unroll
-    for (int ct = 0; ct < MT; ++ct)
-#pragma unroll
-      for (int k = 0; k < 4; ++k) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(q[ct][k], in[ct][k], acc, 0, 0, 0);
-    return acc;
-  };
-  // this wave's activations to the others, theirs back
-  auto share = [&](float* X, const f4& v, f4(&in)[MT]) {
-    if (own) {
-      f4 u;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) u[k] = xelu(v[k]);
-      *(f4*)(X + (mt * 64 + lane) * 4) = u;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int ct = 0; ct < MT; ++ct) in[ct] = *(const f4*)(X + (ct * 64 + lane) * 4);
-  };
-
-  {
-    a = load_bias(bias_conv, mt);
-    f4 wq[KQ];
-#pragma unroll
-    for (int kq = 0; kq < KQ; ++kq) wq[kq] = *(const f4*)(w + ((mt * KQ + kq) * 64 + lane) * 4);
-    if (own) {
-#pragma unroll
-      for (int kq = 0; kq < KQ; ++kq)
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          if (4 * kq + q < KC) a = __builtin_amdgcn_mfma_f32_16x16x4f32(wq[kq][q], ctx[4 * kq + q], a, 0, 0, 0);
-    }
-  }
-  const float* wl = w + L.layer0;
-  const float* bl = bias_conv + C_;
+  const float* wl = w + L.layer0 + ((l >> 4) * MT * 64 + r16) * 4;
+  const float* bl = bias_conv + C_ + l;
+  const float* wc = w + ((l >> 4) * conv_quads(H_) * 64 + r16) * 4;
+  QuadW<1> q[2];
+  q[conv_quads(H_) & 1].load(wc, 0);
+  f4 a[1] = {splat(bias_conv[l])}, z[1];
+  quad_first<H_>(wc, wl, cx, q, a[0]);
   for (int b = 0; b < nb; ++b) {
-    f4 in[MT];
-    load_tile(wl, mt, wn);
-    bn = load_bias(bl, mt);
-    share(xb, a, in);
-    z = own ? chain(wn, in, bn) : bn;
+    z[0] = splat(bl[0]);
+    quad_layer<MT, 1>(wl, 0, wl + layer_stride, quad_act(a[0], lane), q, z);
+    const f4 x = quad_act(z[0], lane);
+    z[0] = splat(bl[C_]);
     wl += layer_stride;
-    bl += C_;
-    load_tile(wl, mt, wn);
-    bn = load_bias(bl, mt);
-    share(hb, z, in);
-    if (own) a = a + chain(wn, in, bn);
+    quad_layer<MT, 1>(wl, 0, wl + layer_stride, x, q, z);
+    a[0] = a[0] + z[0];
     wl += layer_stride;
-    bl += C_;
+    bl += 2 * C_;
   }
-  f4 in[MT], wh[MT];
-  load_tile(w_head, wv, wn);
-  load_tile(w_head, wv + TEAM_WAVES, wh);
-  bn = load_bias(bias_head, wv);
-  z = load_bias(bias_head, wv + TEAM_WAVES);
-  share(xb, a, in);
-  float* row = hb + (lane & 15) * 128 + 4 * g;
-  *(f4*)(row + 16 * wv) = chain(wn, in, bn);
-  *(f4*)(row + 16 * (wv + TEAM_WAVES)) = chain(wh, in, z);
-  __syncthreads();
+  f4 h[2] = {splat(bias_head[lane]), splat(bias_head[64 + lane])};
+  const float* w_head = w + L.layer0 + 2 * nb * layer_stride + ((lane >> 4) * MT * 64 + r16) * 4;
+  QuadW<2> qh[2];
+  qh[0].load(w_head, 4 * MT * 256);
+  quad_layer<MT, 2>(w_head, 4 * MT * 256, w_head, quad_act(a[0], lane), qh, h);
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    hb[v * HB_STRIDE + lane] = h[0][v];
+    hb[v * HB_STRIDE + 64 + lane] = h[1][v];
+  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // ------------------------------------------------------------------ mixture, 16 lanes per pixel
@@ -262,17 +316,12 @@ NXD int serial_pop(SerialStream& S, const f4 (&q)[3], uint32_t pv, int lane, uin
 }
 
 // ------------------------------------------------------------------ lanes
-// LDS of a team after the weights: exchange buffer (the serial pops' tables
-// lie there between the network's uses of it), head table, context window,
-// shared words
-template <int C_>
-constexpr int team_xb_words() {
-  return (C_ / 16) * 256 > SERIAL_WORDS ? (C_ / 16) * 256 : SERIAL_WORDS;
-}
+// LDS of a team after the weights: every wave's head table, the serial pops'
+// tables, context window, shared words
+constexpr int TEAM_HB_WORDS = TEAM_WAVES * 4 * HB_STRIDE;
 constexpr int TEAM_SH_WORDS = 32;
-template <int C_>
-NXHD int64_t team_words(int64_t rows) {
-  return team_xb_words<C_>() + 16 * 128 + (WIN_PLANES * rows / 2 + 3) / 4 * 4 + TEAM_SH_WORDS;
+NXHD int64_t team_words(int64_t rows, bool serial) {
+  return TEAM_HB_WORDS + (serial ? SERIAL_WORDS : 0) + (WIN_PLANES * rows / 2 + 3) / 4 * 4 + TEAM_SH_WORDS;
 }
 
 // KIND of pops: a stream per row of the group or two rows (K = 16, 8), serial
@@ -293,22 +342,25 @@ __global__ void __launch_bounds__(2 * TEAM_WAVES * 64) k_decode_team(DecArgs A) 
   const int wave = uniform((int)(threadIdx.x >> 6));
   const int teams = (int)(blockDim.x / (64 * TEAM_WAVES)), team = wave / TEAM_WAVES, w4 = wave % TEAM_WAVES;
   const int rows = A.team_rows, K = A.K;
-  const int64_t tw = team_words<C_>(rows);
-  float* xb = wts + A.wfloats + team * tw;
-  float* hb = xb + team_xb_words<C_>();
-  int16_t* win = (int16_t*)(hb + 16 * 128);
-  int32_t* sh = (int32_t*)(xb + tw - TEAM_SH_WORDS);
-  float* prm = xb;
-  uint32_t* piv = (uint32_t*)(xb + 16 * SERIAL_PRM);
-  const int o = H_ + 1;
+  const int64_t tw = team_words(rows, KIND == POPS_SERIAL);
+  float* base = wts + A.wfloats + team * tw;
+  float* hb = base + w4 * 4 * HB_STRIDE;
+  float* prm = base + TEAM_HB_WORDS;
+  uint32_t* piv = (uint32_t*)(prm + 16 * SERIAL_PRM);
+  int16_t* win = (int16_t*)(prm + (KIND == POPS_SERIAL ? SERIAL_WORDS : 0));
+  int32_t* sh = (int32_t*)(base + tw - TEAM_SH_WORDS);
+  constexpr int o = H_ + 1;
   const bool live = m < 10;
-  // the pixel (row of the group) whose mixture this lane's row decodes: rows
-  // that share a stream are in one wave (K = 8: r and r + 8; K = 4: r mod 4)
-  const int slot = KIND == POPS_ROWS && K == 8 ? 2 * w4 + (s & 1) + 8 * (s >> 1)
-                   : KIND == POPS_SERIAL && K == 4 ? w4 + 4 * s
-                                                  : 4 * w4 + s;
+  // the pixels (rows of the group) of a wave: four in a row, so that a group of
+  // few rows leaves whole waves free, and with two teams on other SIMDs (wave
+  // w is on SIMD w mod 4); with K = 8, rows r and r + 8 share a stream and a wave
+  const int v4 = (w4 + 2 * team) & (TEAM_WAVES - 1);
+  auto slot_of = [&](int q) { return KIND == POPS_ROWS && K == 8 ? 2 * v4 + (q & 1) + 8 * (q >> 1) : 4 * v4 + q; };
+  const int slot = slot_of(s), nslot = slot_of(lane & 3);  // the mixture's pixel, the network's
+  int off[quad_inputs<H_>()];
+  quad_offsets<H_>(off, rows, lane);
   // barriers of one group
-  const int n_bar = 1 + (2 * A.nb + 2) + (KIND == POPS_SERIAL && K < 4 ? 6 : 0);
+  constexpr int n_bar = 1 + (KIND == POPS_SERIAL ? 6 : 0);
 
   // the team's lane
   int left = 0;        // groups left
@@ -342,7 +394,7 @@ __global__ void __launch_bounds__(2 * TEAM_WAVES * 64) k_decode_team(DecArgs A) 
         Hl = min(D.ph, D.H - y0);
         Wl = min(D.pw, D.W - x0);
         W = D.W;
-        img = D.px;
+        img = D.px + ((int64_t)y0 * D.W + x0) * 3;
         seed = D.seed;
         dump = A.sym_dump ? A.sym_dump + D.px_base * 3 : nullptr;
         bool ok = true;
@@ -457,69 +509,71 @@ __global__ void __launch_bounds__(2 * TEAM_WAVES * 64) k_decode_team(DecArgs A) 
       --left;
       const int na = uniform(min(16, ihi - ts + 1));
       __syncthreads();  // the window as the last group left it
-      {
-        float ctx[conv_chunks(H_)];
-        gather_lds<H_>(ctx, win, rows, gi, min(ts + p, Hl - 1), lane);
-        net_team<H_, C_>(lds_weights(wts), A.nb, ctx, xb, hb, lane, w4);
-      }
       const int i = ts + slot, j = gi - o * i;
       const bool act = slot < na;
+      // a wave without a pixel has nothing to do, or (serial pops) the barriers and its pops
+      const bool some = __ballot(act) != 0ull;
+      if (KIND != POPS_SERIAL && !some) continue;
+      const bool busy = KIND != POPS_SERIAL || some;
       Mix16 M;
-      mix_prep16(hb + slot * 128, m, M);
       uint32_t sl[3] = {0u, 0u, 0u};
-      if constexpr (KIND == POPS_SAMPLE) sample_slots(seed, W, y0 + i, x0 + j, sl);
+      if (busy) {
+        float cx[quad_inputs<H_>()];
+        quad_gather<H_>(cx, off, win, rows, gi, min(ts + nslot, Hl - 1));
+        net_quad<H_, C_>(lds_weights(wts), A.nb, cx, hb, lane);
+        mix_prep16(hb + s * HB_STRIDE, m, M);
+        if constexpr (KIND == POPS_SAMPLE) sample_slots(seed, W, y0 + i, x0 + j, sl);
+      }
       int xv[3] = {0, 0, 0};
       float xr = 0.0f, xg = 0.0f;
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
         Chan16 Q;
-        chan_params16(M, c, xr, xg, Q);
         Mix10 T;
-        row_mix10(Q, T);
-        const uint32_t pv = row_pivots(T, m);
+        uint32_t pv = 0;
+        if (busy) {
+          chan_params16(M, c, xr, xg, Q);
+          row_mix10(Q, T);
+          pv = row_pivots(T, m);
+        }
         int sy = 0;
         uint32_t start = 0, freq = 0;
         if constexpr (KIND == POPS_SAMPLE) {
-          sy = row_search(T, pv, sl[c], m, s, start, freq);
+          if (busy) sy = row_search(T, pv, sl[c], m, s, start, freq);
         } else if constexpr (KIND == POPS_ROWS) {
-          sy = row_pop(T, pv, P, act && (K == 16 || s < 2), m, s, start, freq);
-          if (K == 8) {
-            // rows r and r + 8 share a stream: the second has its turn with
-            // the first's state, and hands it back
-            auto other = [](uint32_t v) { return (uint32_t)__shfl_xor((int)v, 32); };
-            const uint32_t x1 = other(P.x), p1 = other(P.pos);
-            P.x = s < 2 ? P.x : x1;
-            P.pos = s < 2 ? P.pos : p1;
-            if (__ballot(act && s >= 2) != 0ull) {
-              uint32_t st2, fr2;
-              const int sy2 = row_pop(T, pv, P, act && s >= 2, m, s, st2, fr2);
-              sy = s < 2 ? sy : sy2;
-              start = s < 2 ? start : st2;
-              freq = s < 2 ? freq : fr2;
-              const uint32_t x2 = other(P.x), p2 = other(P.pos);
-              P.x = s < 2 ? x2 : P.x;
-              P.pos = s < 2 ? p2 : P.pos;
+          if (busy) {
+            sy = row_pop(T, pv, P, act && (K == 16 || s < 2), m, s, start, freq);
+            if (K == 8) {
+              // rows r and r + 8 share a stream: the second has its turn with
+              // the first's state, and hands it back
+              auto other = [](uint32_t v) { return (uint32_t)__shfl_xor((int)v, 32); };
+              const uint32_t x1 = other(P.x), p1 = other(P.pos);
+              P.x = s < 2 ? P.x : x1;
+              P.pos = s < 2 ? P.pos : p1;
+              if (__ballot(act && s >= 2) != 0ull) {
+                uint32_t st2, fr2;
+                const int sy2 = row_pop(T, pv, P, act && s >= 2, m, s, st2, fr2);
+                sy = s < 2 ? sy : sy2;
+                start = s < 2 ? start : st2;
+                freq = s < 2 ? freq : fr2;
+                const uint32_t x2 = other(P.x), p2 = other(P.pos);
+                P.x = s < 2 ? x2 : P.x;
+                P.pos = s < 2 ? p2 : P.pos;
+              }
             }
           }
         } else {
           // tables of the group's pixels, then each stream's wave pops its rows
-          if (m < 12) {
-            float* e = prm + (slot * 4 + (m & 3)) * 12 + 3 * (m >> 2);
-            e[0] = live ? Q.w : 0.0f;
-            e[1] = live ? Q.a : 0.0f;
-            e[2] = live ? Q.b : 0.0f;
-          }
-          piv[slot * 16 + m] = pv;
-          auto meet = [&]() {
-            if (K < 4) {
-              __syncthreads();
-            } else {  // every row of the stream is this wave's own
-              __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-              __builtin_amdgcn_wave_barrier();
-              __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+          if (busy) {
+            if (m < 12) {
+              float* e = prm + (slot * 4 + (m & 3)) * 12 + 3 * (m >> 2);
+              e[0] = live ? Q.w : 0.0f;
+              e[1] = live ? Q.a : 0.0f;
+              e[2] = live ? Q.b : 0.0f;
             }
-          };
-          meet();
+            piv[slot * 16 + m] = pv;
+          }
+          __syncthreads();
           if (w4 < K) {
             f4 q[3];
             uint32_t pw = 0;
@@ -544,7 +598,7 @@ __global__ void __launch_bounds__(2 * TEAM_WAVES * 64) k_decode_team(DecArgs A) 
               if (dump && lane == 0) dump[((int64_t)(y0 + ts + r) * W + (x0 + gi - o * (ts + r))) * 3 + c] = st1 | (fr1 << 16);
             }
           }
-          meet();
+          __syncthreads();
           sy = sh[8 + slot];
         }
         if (c == 0) xv[0] = sy;
@@ -552,17 +606,15 @@ __global__ void __launch_bounds__(2 * TEAM_WAVES * 64) k_decode_team(DecArgs A) 
         else xv[2] = sy;
         if (KIND == POPS_ROWS && dump && act && m == 0)
           dump[((int64_t)(y0 + i) * W + (x0 + j)) * 3 + c] = start | (freq << 16);
-        if (c == 0) {
+        if (c < 2 && busy) {
           posterior16(M, sy, Q, live);
-          xr = normalise(sy);
-        } else if (c == 1) {
-          posterior16(M, sy, Q, live);
-          xg = normalise(sy);
+          if (c == 0) xr = normalise(sy);
+          else xg = normalise(sy);
         }
       }
       if (act && m < 3) {
         const int v = m == 0 ? xv[0] : (m == 1 ? xv[1] : xv[2]);
-        img[((int64_t)(y0 + i) * W + (x0 + j)) * 3 + m] = (uint8_t)v;
+        img[((uint32_t)i * (uint32_t)W + (uint32_t)j) * 3u + (uint32_t)m] = (uint8_t)v;  // a window's rows: 32 bits hold it
         win_put(win, rows, gi, m, H_ + i, 2 * v - 255);
       }
     }
@@ -612,13 +664,19 @@ NXD void band_publish(int32_t* slot, int32_t v) {
 template <int H_>
 constexpr int band_rows() { return (ROW_BAND + H_ + 3) / 4 * 4; }
 
+// The workgroup has a fifth wave, the band's link to its neighbours: after
+// each step's barrier it publishes the step and fetches the rows above for the
+// next, so that neither the release nor those loads are on the team's path
+// (1,100 of 16,500 cycles a step when the team's first wave did it).
+constexpr int ROW_BLOCK = 64 * (ROW_WAVES + 1);
+
 template <int H_, int C_>
-__device__ void decode_band(const DecArgs& A, const float* w, float* xb, float* hb, int16_t* win, int32_t* sh,
-                            int64_t B) {
+__device__ void decode_band(const DecArgs& A, const float* w, float* hbs, int16_t* win, int32_t* sh, int64_t B) {
   static_assert(ROW_BAND == 16 && ROW_WAVES == 4, "a band is one 16-pixel tile, four rows per wave");
   constexpr int rows = band_rows<H_>();
   const int lane = threadIdx.x & 63, wave = uniform((int)(threadIdx.x >> 6));
-  const int p = lane & 15;                                  // network: the tile's pixel p is band row p
+  const bool link = wave == ROW_WAVES;
+  float* hb = hbs + min(wave, ROW_WAVES - 1) * 4 * HB_STRIDE;
   const int m = lane & 15, s = lane >> 4, pp = 4 * wave + s;  // mixture: component m of band row pp
   const int n = find_img_band(A.desc, A.n_img, B);
   const ImgDesc D = uniform_desc(A.desc + n);
@@ -658,7 +716,7 @@ __device__ void decode_band(const DecArgs& A, const float* w, float* xb, float* 
   // last row's and never pop), in every lane of the row's pixel
   const int64_t ebase = row_entry_base(ly, lx, D.nlx, D.ph, Hl) + r0;
   if (threadIdx.x == 0) sh[0] = 1;
-  for (int k = threadIdx.x; k < WIN_PLANES * rows / 2; k += ROW_WAVES * 64) ((uint32_t*)win)[k] = 0u;
+  for (int k = threadIdx.x; k < WIN_PLANES * rows / 2; k += ROW_BLOCK) ((uint32_t*)win)[k] = 0u;
   __syncthreads();
   PixStream P;
   P.x = 0u;
@@ -688,27 +746,26 @@ __device__ void decode_band(const DecArgs& A, const float* w, float* xb, float* 
     __syncthreads();
     return;
   }
-  uint8_t* img = D.px;
-  const int o = H_ + 1;
+  constexpr int o = H_ + 1;
   const int t_lo = o * r0, t_hi = (Wl - 1) + o * r1;
-  uint32_t* dump = A.sym_dump ? A.sym_dump + D.px_base * 3 : nullptr;
-  // the rows above: lane 3 q + c of the first wave takes channel c of row
-  // r0 - 1 - q; its value of step t (0 where that is off the lane)
-  const int uq = min(lane / 3, H_ - 1), uc = lane - 3 * (lane / 3);
-  auto above = [&](int t) {
-    const int i = r0 - 1 - uq, j = t - o * i;
-    const bool in = bb > 0 && i >= 0 && j >= 0 && j < Wl;
-    const int v = as_global(img)[((int64_t)(y0 + max(i, 0)) * D.W + (x0 + min(max(j, 0), Wl - 1))) * 3 + uc];
-    return in ? 2 * v - 255 : 0;
-  };
-  int32_t seen = bb == 0 ? BAND_DONE : 0;  // steps of the band above known to be finished
-  int ahead = 0;                           // above(t - 1), if loaded a step ahead
-  bool loaded = false;
-  for (int t = t_lo; t <= t_hi; ++t) {
-    if (wave == 0) {
+  if (link) {
+    // lane 3 q + c takes channel c of row r0 - 1 - q: its value of step t, 0
+    // where that is off the lane
+    const uint8_t* img = D.px;
+    const int uq = min(lane / 3, H_ - 1), uc = lane - 3 * (lane / 3);
+    const int i = r0 - 1 - uq;
+    const gbytes row = as_global(img + ((int64_t)(y0 + max(i, 0)) * D.W + x0) * 3 + uc);
+    auto fetch = [&](int t) {
+      const int j = t - o * i;
+      const bool in = bb > 0 && i >= 0 && j >= 0 && j < Wl;
+      const int v = row[3 * min(max(j, 0), Wl - 1)];
+      if (lane < 3 * H_) win_put(win, rows, t, uc, H_ - 1 - uq, in ? 2 * v - 255 : 0);
+    };
+    int32_t seen = bb == 0 ? BAND_DONE : 0;  // steps of the band above known to be finished
+    const int32_t* up = A.progress + (B - 1);
+    for (int t = t_lo; t <= t_hi; ++t) {
       if (seen < t) {
         // wait until the band above has finished step t - 1
-        const int32_t* up = A.progress + (B - 1);
         int32_t v = uniform(__hip_atomic_load(up, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT));
         if (v < t) {
           const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
@@ -723,92 +780,85 @@ __device__ void decode_band(const DecArgs& A, const float* w, float* xb, float* 
         }
         seen = v;
       }
-      if (t == t_lo) {
-        // the window's columns before the band's first step
-        constexpr int Q = H_ * (H_ + 2);
-#pragma unroll
-        for (int d = Q; d > 1; --d) {
-          const int u = above(t - d);
-          if (lane < 3 * H_) win_put(win, rows, t - d, uc, H_ - 1 - uq, u);
-        }
-      }
-      const int v = loaded ? ahead : above(t - 1);
-      if (lane < 3 * H_) win_put(win, rows, t - 1, uc, H_ - 1 - uq, v);
-      loaded = seen > t;
-    }
-    // this band's step t - 1 is finished in every wave (its pixels stored)
-    __syncthreads();
-    if (wave == 0) {
-      if (loaded) ahead = above(t);
+      if (t == t_lo)  // the window's columns before the band's first step
+        for (int d = H_ * (H_ + 2); d > 1; --d) fetch(t - d);
+      fetch(t - 1);
+      // the band's step t - 1 is finished in every wave (its pixels stored)
+      __syncthreads();
       if (lane == 0) band_publish(mine, t);
     }
-    int ilo, ihi;
-    step_rows(t, Hl, Wl, o, ilo, ihi);
-    const int a = max(ilo, r0), bmax = min(ihi, r1);
-    const int i = r0 + pp, j = t - o * i;
-    const bool act = i >= a && i <= bmax;
-    int xv[3] = {0, 0, 0};
-    if (a <= bmax) {  // the same for the whole workgroup
-      {
-        float ctx[conv_chunks(H_)];
-        gather_lds<H_>(ctx, win, rows, t, p, lane);
-        net_team<H_, C_>(lds_weights(w), A.nb, ctx, xb, hb, lane, wave);
-      }
-      const bool live = m < 10;
-      Mix16 M;
-      mix_prep16(hb + pp * 128, m, M);
-      float xr = 0.0f, xg = 0.0f;
+  } else {
+    uint8_t* img = D.px + ((int64_t)(y0 + r0 + pp) * D.W + x0) * 3 + m;  // this lane's row (used where it is one)
+    uint32_t* dump = A.sym_dump ? A.sym_dump + D.px_base * 3 : nullptr;
+    const bool live = m < 10;
+    const int i = r0 + pp;
+    int off[quad_inputs<H_>()];
+    quad_offsets<H_>(off, rows, lane);
+    for (int t = t_lo; t <= t_hi; ++t) {
+      __syncthreads();
+      const int j = t - o * i;
+      const bool act = i <= r1 && j >= 0 && j < Wl;
+      int xv[3] = {0, 0, 0};
+      if (__ballot(act) != 0ull) {
+        {
+          float cx[quad_inputs<H_>()];
+          quad_gather<H_>(cx, off, win, rows, t, 4 * wave + (lane & 3));
+          net_quad<H_, C_>(lds_weights(w), A.nb, cx, hb, lane);
+        }
+        Mix16 M;
+        mix_prep16(hb + s * HB_STRIDE, m, M);
+        float xr = 0.0f, xg = 0.0f;
 #pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        Chan16 Q;
-        chan_params16(M, c, xr, xg, Q);
-        Mix10 T;
-        row_mix10(Q, T);
-        uint32_t start, freq;
-        const int sy = row_pop(T, row_pivots(T, m), P, act, m, s, start, freq);
-        if (c == 0) xv[0] = sy;
-        else if (c == 1) xv[1] = sy;
-        else xv[2] = sy;
-        if (dump && act && m == 0) dump[((int64_t)(y0 + i) * D.W + (x0 + j)) * 3 + c] = start | (freq << 16);
-        if (c == 0) {
-          posterior16(M, sy, Q, live);
-          xr = normalise(sy);
-        } else if (c == 1) {
-          posterior16(M, sy, Q, live);
-          xg = normalise(sy);
+        for (int c = 0; c < 3; ++c) {
+          Chan16 Q;
+          chan_params16(M, c, xr, xg, Q);
+          Mix10 T;
+          row_mix10(Q, T);
+          uint32_t start, freq;
+          const int sy = row_pop(T, row_pivots(T, m), P, act, m, s, start, freq);
+          if (c == 0) xv[0] = sy;
+          else if (c == 1) xv[1] = sy;
+          else xv[2] = sy;
+          if (dump && act && m == 0) dump[((int64_t)(y0 + i) * D.W + (x0 + j)) * 3 + c] = start | (freq << 16);
+          if (c == 0) {
+            posterior16(M, sy, Q, live);
+            xr = normalise(sy);
+          } else if (c == 1) {
+            posterior16(M, sy, Q, live);
+            xg = normalise(sy);
+          }
         }
       }
-    }
-    // the window's column t: the decoded pixels, 0 in the other rows
-    if (m < 3) {
-      const int v = m == 0 ? xv[0] : (m == 1 ? xv[1] : xv[2]);
-      if (act) img[((int64_t)(y0 + i) * D.W + (x0 + j)) * 3 + m] = (uint8_t)v;
-      win_put(win, rows, t, m, H_ + pp, act ? 2 * v - 255 : 0);
+      // the window's column t: the decoded pixels, 0 in the other rows
+      if (m < 3) {
+        const int v = m == 0 ? xv[0] : (m == 1 ? xv[1] : xv[2]);
+        if (act) img[3 * j] = (uint8_t)v;
+        win_put(win, rows, t, m, H_ + pp, act ? 2 * v - 255 : 0);
+      }
     }
   }
   __syncthreads();
   if (threadIdx.x == 0) band_publish(mine, BAND_DONE);
   // every row's stream must end in the start state with every byte read
-  if (pp < nrows && m == 0 && !(P.x == RANS_X0 && P.pos == P.len)) A.status[n] = ST_CORRUPT;
+  if (!link && pp < nrows && m == 0 && !(P.x == RANS_X0 && P.pos == P.len)) A.status[n] = ST_CORRUPT;
   __syncthreads();
 }
 
-// LDS of the row decoder after the weights: exchange buffer, head table,
+// LDS of the row decoder after the weights: the waves' head tables, the
 // context window, then a few shared words
-template <int H_, int C_>
+template <int H_>
 constexpr size_t rows_lds_extra() {
-  return (size_t)((C_ / 16) * 256 + 16 * 128 + WIN_PLANES * band_rows<H_>() / 2 + 4) * sizeof(float);
+  return (size_t)(TEAM_HB_WORDS + WIN_PLANES * band_rows<H_>() / 2 + 4) * sizeof(float);
 }
 
 template <int H_, int C_>
-__global__ void __launch_bounds__(ROW_WAVES * 64) k_decode_rows(DecArgs A) {
+__global__ void __launch_bounds__(ROW_BLOCK) k_decode_rows(DecArgs A) {
   extern __shared__ float4 smem_f4[];
   float* w = (float*)smem_f4;
   load_weights(w, A.w, A.wfloats);
-  float* xb = w + A.wfloats;
-  float* hb = xb + (C_ / 16) * 256;
-  int16_t* win = (int16_t*)(hb + 16 * 128);
-  int32_t* sh = (int32_t*)(hb + 16 * 128 + WIN_PLANES * band_rows<H_>() / 2);  // band and flag words
+  float* hb = w + A.wfloats;
+  int16_t* win = (int16_t*)(hb + TEAM_HB_WORDS);
+  int32_t* sh = (int32_t*)(hb + TEAM_HB_WORDS + WIN_PLANES * band_rows<H_>() / 2);  // band and flag words
   for (;;) {
     if (threadIdx.x == 0) sh[2] = atomicAdd(A.counter, 1);
     __syncthreads();
@@ -818,7 +868,7 @@ __global__ void __launch_bounds__(ROW_WAVES * 64) k_decode_rows(DecArgs A) {
     // the queue's order of the bands (start step, then image and lane), or image order
     const int64_t B = A.band_order ? (int64_t)uniform(A.band_order[Q]) : Q;
     if (B < 0 || B >= A.n_bands) continue;  // only a damaged workspace: never decode out of range
-    decode_band<H_, C_>(A, w, xb, hb, win, sh, B);
+    decode_band<H_, C_>(A, w, hb, win, sh, B);
   }
 }
 
@@ -846,30 +896,19 @@ static hipError_t team_setup_t(bool rows) {
 
 hipError_t prepare_team(int h, int C, bool rows) { NX_DISPATCH(team_setup_t, h, C, rows); }
 
-template <int H_, int C_>
-static size_t team_lds_t(int64_t wfloats, int teams, int rows) {
-  return (size_t)(wfloats + teams * team_words<C_>(rows)) * sizeof(float);
-}
-template <int H_, int C_>
-static hipError_t team_fit_t(int64_t wfloats, int teams, int rows, size_t lim, bool* fits) {
-  *fits = team_lds_t<H_, C_>(wfloats, teams, rows) <= lim;
-  return hipSuccess;
-}
-static hipError_t team_fit(int h, int C, int64_t wfloats, int teams, int rows, size_t lim, bool* fits) {
-  NX_DISPATCH(team_fit_t, h, C, wfloats, teams, rows, lim, fits);
+static size_t team_lds(int64_t wfloats, int teams, int rows, bool serial) {
+  return (size_t)(wfloats + teams * team_words(rows, serial)) * sizeof(float);
 }
 
-int decode_teams(int h, int C, int64_t wfloats, int64_t n_lanes, int order, int64_t rows, int cus, size_t lds) {
+int decode_teams(int K, int64_t wfloats, int64_t n_lanes, int order, int64_t rows, int cus, size_t lds) {
   if (order == 0 || n_lanes < 1 || n_lanes > 2 * (int64_t)cus || rows < 4 || rows > 4096) return 0;
   const int teams = n_lanes > cus ? 2 : 1;
-  bool fits = false;
-  if (team_fit(h, C, wfloats, teams, (int)rows, lds, &fits) != hipSuccess) return 0;
-  return fits ? teams : 0;
+  return team_lds(wfloats, teams, (int)rows, K > 0 && K < 8) <= lds ? teams : 0;
 }
 
 template <int H_, int C_>
 static hipError_t team_t(const DecArgs& a, int kind, int teams, hipStream_t s) {
-  const size_t lds = team_lds_t<H_, C_>(a.wfloats, teams, a.team_rows);
+  const size_t lds = team_lds(a.wfloats, teams, a.team_rows, kind == POPS_SERIAL);
   const dim3 grid((unsigned)((a.n_lanes + teams - 1) / teams)), block((unsigned)(64 * TEAM_WAVES * teams));
   if (kind == POPS_ROWS)
     hipLaunchKernelGGL((k_decode_team<H_, C_, POPS_ROWS>), grid, block, lds, s, a);
@@ -880,17 +919,17 @@ static hipError_t team_t(const DecArgs& a, int kind, int teams, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_decode_team(int h, int C, const DecArgs& a, int teams, bool sample, hipStream_t s) {
+hipError_t launch_decode_team(int h, int C, const DecArgs& a, int teams, hipStream_t s) {
   if (a.n_lanes == 0) return hipSuccess;
-  if (teams < 1 || teams > 2 || (!sample && !valid_interleave(a.K))) return hipErrorInvalidValue;
-  const int kind = sample ? POPS_SAMPLE : a.K >= 8 ? POPS_ROWS : POPS_SERIAL;
+  if (teams < 1 || teams > 2 || (a.K != 0 && !valid_interleave(a.K))) return hipErrorInvalidValue;
+  const int kind = a.K == 0 ? POPS_SAMPLE : a.K >= 8 ? POPS_ROWS : POPS_SERIAL;
   NX_DISPATCH(team_t, h, C, a, kind, teams, s);
 }
 
 template <int H_, int C_>
 static hipError_t rows_t(const DecArgs& a, int grid, hipStream_t s) {
-  const size_t lds = (size_t)a.wfloats * 4 + rows_lds_extra<H_, C_>();
-  hipLaunchKernelGGL((k_decode_rows<H_, C_>), dim3(grid), dim3(ROW_WAVES * 64), lds, s, a);
+  const size_t lds = (size_t)a.wfloats * 4 + rows_lds_extra<H_>();
+  hipLaunchKernelGGL((k_decode_rows<H_, C_>), dim3(grid), dim3(ROW_BLOCK), lds, s, a);
   return hipGetLastError();
 }
 
