@@ -710,7 +710,7 @@ static nellox_status run_impl(nellox_model* m, const nellox_decode_plan* plan, c
     a.team_rows = (int)plan->ring_rows;
     e = launch_decode_team(m->h, m->Cp, a, teams, s);
   } else {
-    e = launch_decode(m->h, m->Cp, a, plan->grid, plan->waves, s);
+    e = launch_decode(m->h, m->Cp, a, plan->grid, plan->waves, m->lds, s);
   }
   if (e != hipSuccess) return hip_fail(e, "decoder launch");
   return NELLOX_OK;
@@ -817,7 +817,7 @@ nellox_status nellox_sample(const nellox_model* mc, int32_t n, const uint64_t* s
   int grid = 0, waves = 0;
   decode_shape(P.n_lanes, persistent_grid(m), grid, waves);
   a.team_rows = (int)rows;
-  e = teams ? launch_decode_team(m->h, m->Cp, a, teams, s) : launch_sample(m->h, m->Cp, a, grid, waves, s);
+  e = teams ? launch_decode_team(m->h, m->Cp, a, teams, s) : launch_sample(m->h, m->Cp, a, grid, waves, m->lds, s);
   if (e != hipSuccess) return hip_fail(e, "sampler launch");
   return NELLOX_OK;
 }

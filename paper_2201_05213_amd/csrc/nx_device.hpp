@@ -162,6 +162,8 @@ struct TapCodes {
   }
 };
 
+NXD int uniform_int(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
 // global-memory view of a byte pointer (lets the compiler use global loads)
 typedef const __attribute__((address_space(1))) uint8_t* gbytes;
 NXD gbytes as_global(const uint8_t* p) { return (gbytes)p; }
@@ -280,22 +282,42 @@ NXD void gather(float (&ctx)[conv_chunks(H_)], const TapCodes<H_>& tc, const uin
 // column t - h(h+2) + (h+1) dy + dx, always a column before t. The window
 // holds the int16 numerators 2x - 255 with 0 off the lane, so no bounds test
 // is needed and the value is the unsheared gather's, bit for bit. i must be
-// a row of the lane (callers clamp inactive rows).
+// a row of the lane (callers clamp inactive rows, whose contexts go unused).
+// Input k is plane 3 (t - Q) + k - 3 h dy (mod 48): the four lane groups' inputs
+// of a K-chunk are four planes in a row, whose first is the same for the whole
+// wave; groups past plane 47 go back to 0, and a chunk that straddles two window
+// rows picks one of two firsts. 3 vector instructions a tap, where finding
+// each tap's own column took 13.
+NXD int ring_at(const int16_t* ring, int64_t base, uint32_t at) {
+  return *(const __attribute__((address_space(1))) int16_t*)(as_global((const uint8_t*)ring) + base + at);
+}
 template <int H_>
-NXD void gather_ring(float (&ctx)[conv_chunks(H_)], const TapCodes<H_>& tc, const int16_t* ring, int rows, int t,
-                     int i, bool active) {
-  constexpr int o = H_ + 1, Q = H_ * (H_ + 2);
-  const __attribute__((address_space(1))) int16_t* g = (const __attribute__((address_space(1))) int16_t*)ring;
+NXD void gather_ring(float (&ctx)[conv_chunks(H_)], const int16_t* ring, int rows, int t, int i) {
+  constexpr int Q = H_ * (H_ + 2), R = 3 * (2 * H_ + 1), PLANES = 3 * RING_COLS;
+  const int g = (threadIdx.x >> 4) & 3;
+  const int s = 3 * ((t - Q) & (RING_COLS - 1));
+  // bytes; a place that isn't wrapped is the larger, over a base 48 planes low
+  const uint32_t at = (uint32_t)(2 * (g * rows + i)), unwrapped = at + (uint32_t)(2 * PLANES * rows);
   int raw[conv_chunks(H_)];
 #pragma unroll
   for (int kc = 0; kc < conv_chunks(H_); ++kc) {
-    const uint32_t code = (tc.w[kc >> 2] >> (8 * (kc & 3))) & 0xffu;
-    const int dy = (int)(code & 3u), dx = (int)((code >> 2) & 7u), ch = (int)(code >> 5);
-    const int col = (t - Q + o * dy + dx) & (RING_COLS - 1);
-    raw[kc] = g[(uint32_t)((col * 3 + ch) * rows + i + dy)];
+    const int d0 = min(4 * kc / R, H_), d1 = min((4 * kc + 3) / R, H_);
+    auto first = [&](int dy) {
+      const int p = s + 4 * kc - 3 * H_ * dy;
+      return uniform_int(p >= PLANES ? p - PLANES : p);
+    };
+    const int f0 = first(d0), f1 = first(d1);
+    if (d0 == d1) {
+      raw[kc] = ring_at(ring, 2 * ((int64_t)(f0 - PLANES) * rows + d0), g >= PLANES - f0 ? at : unwrapped);
+    } else {
+      const bool upper = 4 * kc + g >= R * d1;
+      const int f = upper ? f1 : f0;
+      const uint32_t row = (uint32_t)(upper ? 2 * (f1 * rows + d1) : 2 * (f0 * rows + d0));
+      raw[kc] = ring_at(ring, 0, row + at - (g >= PLANES - f ? (uint32_t)(2 * PLANES * rows) : 0u));
+    }
   }
 #pragma unroll
-  for (int kc = 0; kc < conv_chunks(H_); ++kc) ctx[kc] = (float)(active ? raw[kc] : 0) * (1.0f / 255.0f);
+  for (int kc = 0; kc < conv_chunks(H_); ++kc) ctx[kc] = (float)raw[kc] * (1.0f / 255.0f);
 }
 
 // ------------------------------------------------------------------ network
@@ -401,6 +423,213 @@ NXD void net_forward(const float* __restrict__ w, int nb, const float (&ctx)[con
   sink(2 * nb, u);
   bias_init(head, bias_head, g);
   layer_mm<HEAD_TILES, MT>(w_head, u, head, lane);
+}
+
+// ------------------------------------------------------------------ network, four pixels at a time
+// The network of NQ times four pixels on one wave. v_mfma_f32_4x4x1f32 adds 16
+// outer products (blocks) of 4 x 4; with the activations as its A operand, one
+// block's four pixels broadcast to all (cbsz 4, block abid), and the weights
+// as B, it is one input k of 64 outputs: lane l has output l, register v pixel
+// v, and A's block abid has input k of pixel r in lane 4 abid + r. Inputs are
+// added one by one in the order of the 16x16x4 form, which rounds the same
+// (each is a chain of fused multiply-adds). A layer's outputs become the next
+// one's A operand by a 4 x 4 transpose within each four lanes. (C < 64: the
+// lanes past C repeat the others.)
+// It does the work of its pixels alone: net_forward's tile takes 32 cycles an
+// instruction for 16 pixels, this 8 for four, or 12.5 where the wave is alone
+// on its SIMD and NQ is 1 (each waits for the last). Used where a group has few
+// pixels, and by teams, whose waves take four pixels each: split by output
+// tiles instead, a team's layers cost six exchanges through LDS a group, 600
+// cycles each (model B's network 7.3 thousand cycles a group so, about 6 as
+// here; one 1024 x 1024 image with a stream per row, with the link wave:
+// 34.6 -> 29.9 ms).
+constexpr int quad_inputs(int h) { return (4 * conv_chunks(h) + 15) / 16; }
+constexpr int HB_STRIDE = 132;  // floats per pixel of a head table
+template <int A>
+NXD f4 quad_mfma(float act, float w, f4 d) { return __builtin_amdgcn_mfma_f32_4x4x1f32(act, w, d, 4, A, 0); }
+
+template <int CTRL>
+NXD float quad_dpp(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+// x[j] of lane 4 a + r = u[r] of lane 4 a + j
+NXD f4 quad_transpose(const f4& u, int lane) {
+  const bool o0 = lane & 1, o1 = lane & 2;
+  // (all lanes exchange, then each picks: no branch around an exchange)
+  f4 e, y, x;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) e[c] = quad_dpp<0xB1>(u[c ^ 1]);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) y[c] = o0 == ((c & 1) != 0) ? u[c] : e[c];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) e[c] = quad_dpp<0x4E>(y[c ^ 2]);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) x[c] = o1 == ((c & 2) != 0) ? y[c] : e[c];
+  return x;
+}
+template <int NQ>
+NXD void quad_act(const f4 (&a)[NQ], f4 (&x)[NQ], int lane) {
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    f4 u;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) u[v] = xelu(a[q][v]);
+    x[q] = quad_transpose(u, lane);
+  }
+}
+template <int NQ>
+NXD void quad_splat(f4 (&a)[NQ], float b) {
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) a[q] = f4{b, b, b, b};
+}
+
+// The weights of 16 inputs, N outputs a lane (rows `stride` floats apart): four
+// 16-byte reads of LDS each. They are issued a chunk of 16 inputs ahead of
+// their use (the barrier to scheduling keeps them there): read where they are
+// used, they cost a wait of about 130 cycles in every chunk of 200.
+template <int N>
+struct QuadW {
+  f4 v[4][N];
+  NXD void load(const float* w, int stride) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+#pragma unroll
+      for (int n = 0; n < N; ++n) v[g][n] = *(const f4*)(w + n * stride + 64 * g);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+};
+// 16 inputs of block 4 CT's lanes on: chunk (ct, q) of the 16x16x4 form holds
+// inputs 16 ct + 4 g + q, g = 0 .. 3, and their order is the order here
+template <int CT, int N, int NQ, int Q = 0, int G = 0>
+NXD void quad_chunk(const QuadW<N>& w, const f4 (&x)[NQ], f4 (&d)[N][NQ]) {
+#pragma unroll
+  for (int n = 0; n < N; ++n)
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) d[n][q] = quad_mfma<4 * CT + G>(x[q][Q], w.v[G][n][Q], d[n][q]);
+  if constexpr (G < 3) quad_chunk<CT, N, NQ, Q, G + 1>(w, x, d);
+  else if constexpr (Q < 3) quad_chunk<CT, N, NQ, Q + 1, 0>(w, x, d);
+}
+// a layer of 16 CTS inputs; w[0] holds its first chunk, and in the end what
+// `next` points at
+template <int CTS, int N, int NQ, int CT = 0>
+NXD void quad_layer(const float* wl, int stride, const float* next, const f4 (&x)[NQ], QuadW<N> (&w)[2],
+                    f4 (&d)[N][NQ]) {
+  w[(CT + 1) & 1].load(CT + 1 < CTS ? wl + (CT + 1) * 256 : next, stride);
+  quad_chunk<CT, N, NQ>(w[CT & 1], x, d);
+  if constexpr (CT + 1 < CTS) quad_layer<CTS, N, NQ, CT + 1>(wl, stride, next, x, w, d);
+  else if constexpr (CTS & 1) w[0] = w[1];
+}
+// inputs 16 kq .. of the first layer (there in ascending order)
+template <int H_, int KQ_, int NQ, int Q = 0, int G = 0>
+NXD void quad_first_chunk(const QuadW<1>& w, const float (&cx)[NQ][quad_inputs(H_)], f4 (&d)[NQ]) {
+  if constexpr (4 * KQ_ + Q < conv_chunks(H_)) {
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) d[q] = quad_mfma<4 * Q + G>(cx[q][KQ_], w.v[G][0][Q], d[q]);
+    if constexpr (G < 3) quad_first_chunk<H_, KQ_, NQ, Q, G + 1>(w, cx, d);
+    else if constexpr (Q < 3) quad_first_chunk<H_, KQ_, NQ, Q + 1, 0>(w, cx, d);
+  }
+}
+template <int H_, int NQ, int KQ_ = 0>
+NXD void quad_first(const float* wl, const float* next, const float (&cx)[NQ][quad_inputs(H_)], QuadW<1> (&w)[2],
+                    f4 (&d)[NQ]) {
+  constexpr int KQ = conv_quads(H_), P = (KQ_ + KQ) & 1;  // the last chunk in w[1]
+  w[P ^ 1].load(KQ_ + 1 < KQ ? wl + (KQ_ + 1) * 256 : next, 0);
+  quad_first_chunk<H_, KQ_, NQ>(w[P], cx, d);
+  if constexpr (KQ_ + 1 < KQ) quad_first<H_, NQ, KQ_ + 1>(wl, next, cx, w, d);
+}
+
+// cx[q][j]: lane 4 a + r has input 16 j + a of pixel 4 q + r. Head row R of
+// pixel P goes to hb[P HB_STRIDE + R], readable by the wave on return.
+template <int H_, int C_, int NQ>
+NXD void net_quad(const float* __restrict__ w, int nb, const float (&cx)[NQ][quad_inputs(H_)], float* hb, int lane) {
+  constexpr int MT = C_ / 16;
+  const WeightLayout L = weight_layout(H_, C_, 0);
+  const int l = lane & (C_ - 1), r16 = lane & 15;
+  const int layer_stride = MT * MT * 256;
+  const float* bias_conv = w + L.head + HEAD_TILES * MT * 256 + 2 * nb * layer_stride;
+  const float* bias_head = bias_conv + C_ + 2 * nb * C_;
+  const float* wl = w + L.layer0 + ((l >> 4) * MT * 64 + r16) * 4;
+  const float* bl = bias_conv + C_ + l;
+  const float* wc = w + ((l >> 4) * conv_quads(H_) * 64 + r16) * 4;
+  QuadW<1> q[2];
+  q[conv_quads(H_) & 1].load(wc, 0);
+  f4 a[NQ], x[NQ], z[1][NQ];
+  quad_splat(a, bias_conv[l]);
+  quad_first<H_, NQ>(wc, wl, cx, q, a);
+  for (int b = 0; b < nb; ++b) {
+    quad_splat(z[0], bl[0]);
+    quad_act(a, x, lane);
+    quad_layer<MT, 1, NQ>(wl, 0, wl + layer_stride, x, q, z);
+    quad_act(z[0], x, lane);
+    quad_splat(z[0], bl[C_]);
+    wl += layer_stride;
+    quad_layer<MT, 1, NQ>(wl, 0, wl + layer_stride, x, q, z);
+#pragma unroll
+    for (int k = 0; k < NQ; ++k) a[k] = a[k] + z[0][k];
+    wl += layer_stride;
+    bl += 2 * C_;
+  }
+  f4 h[2][NQ];
+  quad_splat(h[0], bias_head[lane]);
+  quad_splat(h[1], bias_head[64 + lane]);
+  const float* w_head = w + L.layer0 + 2 * nb * layer_stride + ((lane >> 4) * MT * 64 + r16) * 4;
+  QuadW<2> qh[2];
+  qh[0].load(w_head, 4 * MT * 256);
+  quad_act(a, x, lane);
+  quad_layer<MT, 2, NQ>(w_head, 4 * MT * 256, w_head, x, qh, h);
+#pragma unroll
+  for (int k = 0; k < NQ; ++k)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      hb[(4 * k + v) * HB_STRIDE + lane] = h[0][k][v];
+      hb[(4 * k + v) * HB_STRIDE + 64 + lane] = h[1][k][v];
+    }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Contexts for net_quad of a pixel per lane 4 a + r: each lane loads its
+// inputs k = 16 j + a, clamped into the lane's pixels and masked as
+// gather_clamped does, or from the sheared window as gather_ring does.
+template <int H_>
+NXD void quad_tap(int j, int lane, int& k, int& dy) {
+  k = min(16 * j + (lane >> 2), 4 * conv_chunks(H_) - 1);
+  dy = min(k / (3 * (2 * H_ + 1)), H_);
+}
+template <int H_>
+NXD void quad_gather_image(float (&cx)[quad_inputs(H_)], const uint8_t* img, int W, int y0, int x0, int Hl, int Wl, int i,
+                           int j, int lane) {
+  const gbytes g = as_global(img);
+  int raw[quad_inputs(H_)], ok[quad_inputs(H_)];
+#pragma unroll
+  for (int n = 0; n < quad_inputs(H_); ++n) {
+    int k, dy;
+    quad_tap<H_>(n, lane, k, dy);
+    const int e = k - 3 * (2 * H_ + 1) * dy, dx = e / 3, ch = e - 3 * dx;
+    const int y = i - H_ + dy, x = j - H_ + dx;
+    ok[n] = -(int)(((unsigned)y < (unsigned)Hl) & ((unsigned)x < (unsigned)Wl));
+    raw[n] = g[((int64_t)(y0 + min(max(y, 0), Hl - 1)) * W + (x0 + min(max(x, 0), Wl - 1))) * 3 + ch];
+  }
+#pragma unroll
+  for (int n = 0; n < quad_inputs(H_); ++n) cx[n] = (float)((2 * raw[n] - 255) & ok[n]) * (1.0f / 255.0f);
+}
+template <int H_>
+NXD void quad_gather_ring(float (&cx)[quad_inputs(H_)], const int16_t* ring, int rows, int t, int i, int lane) {
+  constexpr int Q = H_ * (H_ + 2), PLANES = 3 * RING_COLS;
+  const int s = 3 * ((t - Q) & (RING_COLS - 1));
+  int raw[quad_inputs(H_)];
+#pragma unroll
+  for (int n = 0; n < quad_inputs(H_); ++n) {
+    int k, dy;
+    quad_tap<H_>(n, lane, k, dy);
+    // tap (dy, dx), channel ch is plane 3 ((t - Q) + (h + 1) dy + dx) + ch = 3 (t - Q) + k - 3 h dy
+    uint32_t plane = (uint32_t)(s + k - 3 * H_ * dy);
+    plane = min(plane, plane - (uint32_t)PLANES);
+    raw[n] = ring_at(ring, 0, 2u * (plane * (uint32_t)rows + (uint32_t)(i + dy)));
+  }
+#pragma unroll
+  for (int n = 0; n < quad_inputs(H_); ++n) cx[n] = (float)raw[n] * (1.0f / 255.0f);
 }
 
 // ------------------------------------------------------------------ mixture

@@ -13,6 +13,7 @@
 
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "nx_coder.hpp"
 
@@ -795,7 +796,7 @@ NXD int pop_own(const Chan& Q, PixStream& P, bool act, uint32_t& start, uint32_t
 // for all rows of a group at once (their slots do not depend on each other).
 // SHEAR: the sheared layout (order 2): contexts from the wave's window of the
 // lane's sheared canvas instead of the output image.
-template <int H_, int C_, bool TRACE, int K, bool SAMPLE, bool SHEAR>
+template <int H_, int C_, int K, bool SAMPLE, bool SHEAR>
 __device__ void decode_lane(const DecArgs& A, const float* w, uint32_t* piv, int64_t L, int lane) {
   static_assert(!SAMPLE || K == 4, "sampling is instantiated once, as K = 4");
   const int p = lane & 15, g = lane >> 4;
@@ -943,7 +944,7 @@ __device__ void decode_lane(const DecArgs& A, const float* w, uint32_t* piv, int
     __threadfence_block();
   }
   const int64_t ngroups = raster ? (int64_t)Hl * Wl : (int64_t)Wl + (int64_t)o * (Hl - 1);
-  uint32_t* dump = TRACE ? A.sym_dump + D.px_base * 3 : nullptr;
+  uint32_t* dump = A.sym_dump ? A.sym_dump + D.px_base * 3 : nullptr;
   TapCodes<H_> tc;
   tc.init(g);
 
@@ -978,17 +979,46 @@ __device__ void decode_lane(const DecArgs& A, const float* w, uint32_t* piv, int
       const int i = ts + p;
       const bool active = p < na;
       const int j = raster ? (int)(gi - (int64_t)ilo * Wl) : (int)gi - o * i;
-      float ctx[conv_chunks(H_)];
-      tc.refresh();
-      if constexpr (shear)
-        gather_ring<H_>(ctx, tc, ring, rows, (int)gi, min(i, Hl - 1), active);
-      else
-        gather<H_>(ctx, tc, img, D.W, y0, x0, Hl, Wl, i, j, y0 + ts);
       // sampling: the slots of pixel p (every lane group draws the same)
       uint32_t sl[3] = {0u, 0u, 0u};
       if constexpr (SAMPLE) sample_slots(D.seed, D.W, y0 + i, x0 + j, sl);
       f4 head[HEAD_TILES];
-      net_forward<H_, C_>(lds_weights(w), A.nb, ctx, head, lane);
+      if (na <= A.quad_px) {
+        // few pixels: eight, then four at a time (see net_quad), through a
+        // head table in the wave's LDS
+        float* hb = (float*)piv;
+        int ql = lane;
+        asm("" : "+v"(ql));  // (what follows from it is found here: kept through the loop, it would spill)
+        auto quads = [&](auto nq, int q0) {
+          constexpr int NQ = decltype(nq)::value;
+          float cx[NQ][quad_inputs(H_)];
+#pragma unroll
+          for (int q = 0; q < NQ; ++q) {
+            const int qi = min(ts + q0 + 4 * q + (ql & 3), Hl - 1);
+            if constexpr (shear)
+              quad_gather_ring<H_>(cx[q], ring, rows, (int)gi, qi, ql);
+            else
+              quad_gather_image<H_>(cx[q], img, D.W, y0, x0, Hl, Wl, qi, raster ? j : (int)gi - o * qi, ql);
+          }
+          net_quad<H_, C_, NQ>(lds_weights(w), A.nb, cx, hb + q0 * HB_STRIDE, ql);
+        };
+        int q0 = 0;
+        for (; na - q0 > 4; q0 += 8) quads(std::integral_constant<int, 2>(), q0);
+        if (q0 < na) quads(std::integral_constant<int, 1>(), q0);
+        const float* hp = hb + min(p, na - 1) * HB_STRIDE + 4 * g;
+#pragma unroll
+        for (int mt = 0; mt < HEAD_TILES; ++mt) head[mt] = *(const f4*)(hp + 16 * mt);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+      } else {
+        float ctx[conv_chunks(H_)];
+        tc.refresh();
+        if constexpr (shear)
+          gather_ring<H_>(ctx, ring, rows, (int)gi, min(i, Hl - 1));
+        else
+          gather<H_>(ctx, tc, img, D.W, y0, x0, Hl, Wl, i, j, y0 + ts);
+        net_forward<H_, C_>(lds_weights(w), A.nb, ctx, head, lane);
+      }
       Mix M;
       mix_prep(head, M, has2);
       int xv[3] = {0, 0, 0};
@@ -1027,7 +1057,7 @@ __device__ void decode_lane(const DecArgs& A, const float* w, uint32_t* piv, int
               else if (c == 1) xv[1] = sy;
               else xv[2] = sy;
             }
-            if (TRACE && act && g == 0)
+            if (dump && act && g == 0)
               dump[((int64_t)(y0 + i) * D.W + (x0 + j)) * 3 + c] = start | (freq << 16);
             if constexpr (K == 8) {
               // rows p and p + 8 share a stream: the other half takes the new state
@@ -1098,7 +1128,7 @@ __device__ void decode_lane(const DecArgs& A, const float* w, uint32_t* piv, int
               else if (c == 1) xv[1] = sv;
               else xv[2] = sv;
             }
-            if (TRACE && act && p == 0) {
+            if (dump && act && p == 0) {
               const int ii = ts + pr;
               const int jj = raster ? (int)(gi - (int64_t)ilo * Wl) : (int)gi - o * ii;
               dump[((int64_t)(y0 + ii) * D.W + (x0 + jj)) * 3 + c] = start | (freq << 16);
@@ -1190,7 +1220,7 @@ __device__ void decode_lane(const DecArgs& A, const float* w, uint32_t* piv, int
               else if (c == 1) xv[1] = sym[k];
               else xv[2] = sym[k];
             }
-            if (TRACE && act) {  // every lane stores the same value
+            if (dump && act) {  // every lane stores the same value
               const int ii = ts + q0 + k;
               const int jj = raster ? (int)(gi - (int64_t)ilo * Wl) : (int)gi - o * ii;
               dump[((int64_t)(y0 + ii) * D.W + (x0 + jj)) * 3 + c] = start[k] | (freq[k] << 16);
@@ -1235,13 +1265,13 @@ __device__ void decode_lane(const DecArgs& A, const float* w, uint32_t* piv, int
   if (!clean) A.status[n] = ST_CORRUPT;
 }
 
-template <int H_, int C_, bool TRACE, int K, bool SAMPLE, bool SHEAR>
+template <int H_, int C_, int K, bool SAMPLE, bool SHEAR>
 __global__ void __launch_bounds__(NWAVES_DEC * 64) k_decode(DecArgs A) {
   extern __shared__ float4 smem_f4[];
   float* w = (float*)smem_f4;
   load_weights(w, A.w, A.wfloats);
   const int lane = threadIdx.x & 63;
-  uint32_t* piv = (uint32_t*)(w + A.wfloats) + (threadIdx.x >> 6) * WAVE_LDS_WORDS;
+  uint32_t* piv = (uint32_t*)(w + A.wfloats) + (threadIdx.x >> 6) * A.wave_words;
   for (;;) {
     // one queue pop per wave, by its first active lane, broadcast
     const int leader = uniform(lane);
@@ -1249,7 +1279,7 @@ __global__ void __launch_bounds__(NWAVES_DEC * 64) k_decode(DecArgs A) {
     if (lane == leader) L = atomicAdd(A.counter, 1);
     L = uniform(L);
     if ((int64_t)L >= A.n_lanes) break;
-    decode_lane<H_, C_, TRACE, K, SAMPLE, SHEAR>(A, w, piv, L, lane);
+    decode_lane<H_, C_, K, SAMPLE, SHEAR>(A, w, piv, L, lane);
   }
 }
 
@@ -1356,13 +1386,24 @@ static hipError_t pass_t(const PassArgs& a, int grid, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int H_, int C_, bool TRACE, int K, bool SAMPLE = false>
-static hipError_t decode_tt(const DecArgs& a, int grid, int waves, hipStream_t s) {
-  const size_t lds = (size_t)a.wfloats * 4 + (size_t)waves * WAVE_LDS_WORDS * 4;
+// A wave's LDS: pivot and mixture tables, or a head table of as many pixels
+// (a multiple of 4, at most 12) as the LDS left by the weights gives each
+// wave. Groups of at most that many pixels take net_quad, at 3,650 cycles of
+// matrix instructions per four pixels (model B) against 14,600 for a tile.
+// Measured with the sheared window's shorter gather, 4 1024 x 1024 and 2
+// 2048 x 1536 images in 82 x 64 patches (96 of a patch's 388 steps have at
+// most 12 rows): 8.71 -> 8.35 ms.
+template <int H_, int C_, int K, bool SAMPLE = false>
+static hipError_t decode_tt(const DecArgs& args, int grid, int waves, size_t lim, hipStream_t s) {
+  DecArgs a = args;
+  const int64_t left = ((int64_t)lim / 4 - a.wfloats) / waves;
+  a.quad_px = (int)std::min<int64_t>(12, left / HB_STRIDE / 4 * 4);
+  a.wave_words = std::max(WAVE_LDS_WORDS, a.quad_px * HB_STRIDE);
+  const size_t lds = ((size_t)a.wfloats + (size_t)waves * a.wave_words) * 4;
   if (a.order == 2)
-    hipLaunchKernelGGL((k_decode<H_, C_, TRACE, K, SAMPLE, true>), dim3(grid), dim3(waves * 64), lds, s, a);
+    hipLaunchKernelGGL((k_decode<H_, C_, K, SAMPLE, true>), dim3(grid), dim3(waves * 64), lds, s, a);
   else
-    hipLaunchKernelGGL((k_decode<H_, C_, TRACE, K, SAMPLE, false>), dim3(grid), dim3(waves * 64), lds, s, a);
+    hipLaunchKernelGGL((k_decode<H_, C_, K, SAMPLE, false>), dim3(grid), dim3(waves * 64), lds, s, a);
   return hipGetLastError();
 }
 
@@ -1375,10 +1416,9 @@ static hipError_t decode_setup_k() {
   hipError_t e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&lim, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
   for (int sh = 0; sh < 2 && e == hipSuccess; ++sh) {
-    if (e == hipSuccess) e = allow_lds(sh ? k_decode<H_, C_, false, K, false, true> : k_decode<H_, C_, false, K, false, false>, (size_t)lim);
-    if (e == hipSuccess) e = allow_lds(sh ? k_decode<H_, C_, true, K, false, true> : k_decode<H_, C_, true, K, false, false>, (size_t)lim);
+    if (e == hipSuccess) e = allow_lds(sh ? k_decode<H_, C_, K, false, true> : k_decode<H_, C_, K, false, false>, (size_t)lim);
     if (K == 4 && e == hipSuccess)
-      e = allow_lds(sh ? k_decode<H_, C_, false, 4, true, true> : k_decode<H_, C_, false, 4, true, false>, (size_t)lim);
+      e = allow_lds(sh ? k_decode<H_, C_, 4, true, true> : k_decode<H_, C_, 4, true, false>, (size_t)lim);
   }
   return e;
 }
@@ -1392,23 +1432,18 @@ static hipError_t decode_setup(int K) {
   return decode_setup_k<H_, C_, 1>();
 }
 
-template <int H_, int C_, int K>
-static hipError_t decode_k(const DecArgs& a, int grid, int waves, hipStream_t s) {
-  return a.sym_dump ? decode_tt<H_, C_, true, K>(a, grid, waves, s) : decode_tt<H_, C_, false, K>(a, grid, waves, s);
+template <int H_, int C_>
+static hipError_t sample_t(const DecArgs& a, int grid, int waves, size_t lim, hipStream_t s) {
+  return decode_tt<H_, C_, 4, true>(a, grid, waves, lim, s);
 }
 
 template <int H_, int C_>
-static hipError_t sample_t(const DecArgs& a, int grid, int waves, hipStream_t s) {
-  return decode_tt<H_, C_, false, 4, true>(a, grid, waves, s);
-}
-
-template <int H_, int C_>
-static hipError_t decode_t(const DecArgs& a, int grid, int waves, hipStream_t s) {
-  if (a.K == 2) return decode_k<H_, C_, 2>(a, grid, waves, s);
-  if (a.K == 4) return decode_k<H_, C_, 4>(a, grid, waves, s);
-  if (a.K == 8) return decode_k<H_, C_, 8>(a, grid, waves, s);
-  if (a.K == 16) return decode_k<H_, C_, 16>(a, grid, waves, s);
-  return decode_k<H_, C_, 1>(a, grid, waves, s);
+static hipError_t decode_t(const DecArgs& a, int grid, int waves, size_t lim, hipStream_t s) {
+  if (a.K == 2) return decode_tt<H_, C_, 2>(a, grid, waves, lim, s);
+  if (a.K == 4) return decode_tt<H_, C_, 4>(a, grid, waves, lim, s);
+  if (a.K == 8) return decode_tt<H_, C_, 8>(a, grid, waves, lim, s);
+  if (a.K == 16) return decode_tt<H_, C_, 16>(a, grid, waves, lim, s);
+  return decode_tt<H_, C_, 1>(a, grid, waves, lim, s);
 }
 
 hipError_t launch_pass(int h, int C, const PassArgs& a, int grid, hipStream_t s) {
@@ -1418,16 +1453,16 @@ hipError_t launch_pass(int h, int C, const PassArgs& a, int grid, hipStream_t s)
 
 hipError_t prepare_decode(int h, int C, int K) { NX_DISPATCH(decode_setup, h, C, K); }
 
-hipError_t launch_decode(int h, int C, const DecArgs& a, int grid, int waves, hipStream_t s) {
+hipError_t launch_decode(int h, int C, const DecArgs& a, int grid, int waves, size_t lim, hipStream_t s) {
   if (a.n_lanes == 0) return hipSuccess;
   if (waves < 1 || waves > NWAVES_DEC) return hipErrorInvalidValue;
-  NX_DISPATCH(decode_t, h, C, a, grid, waves, s);
+  NX_DISPATCH(decode_t, h, C, a, grid, waves, lim, s);
 }
 
-hipError_t launch_sample(int h, int C, const DecArgs& a, int grid, int waves, hipStream_t s) {
+hipError_t launch_sample(int h, int C, const DecArgs& a, int grid, int waves, size_t lim, hipStream_t s) {
   if (a.n_lanes == 0) return hipSuccess;
   if (waves < 1 || waves > NWAVES_DEC) return hipErrorInvalidValue;
-  NX_DISPATCH(sample_t, h, C, a, grid, waves, s);
+  NX_DISPATCH(sample_t, h, C, a, grid, waves, lim, s);
 }
 
 template <int O, int K>

@@ -95,6 +95,7 @@ struct DecArgs {
   uint8_t* ring;           // order 2: grid x waves context rings of ring_wave_bytes(ring_rows)
   int ring_rows;
   int team_rows;           // teams: rows of a team's context window in LDS
+  int wave_words, quad_px; // a wave's LDS in words; groups of at most quad_px pixels take net_quad (set at launch)
   int32_t* progress;       // row streams: per band, the steps it has finished (zeroed by the prep)
   int64_t n_bands;         // row streams: bands of the batch (the queue's work items)
   uint64_t band_wait_ticks;  // row streams: the longest wait on the band above (100 MHz clock ticks)
@@ -183,12 +184,12 @@ hipError_t launch_decode_team(int h, int C, const DecArgs& a, int teams, hipStre
 hipError_t prepare_team(int h, int C, bool rows);
 // raise the decoder kernels' LDS limit (once, outside any stream capture)
 hipError_t prepare_decode(int h, int C, int K);
-// waves per workgroup in 1..DECODE_WAVES (the LDS takes one pivot table per wave);
+// waves per workgroup in 1..DECODE_WAVES (the LDS, of at most `lds` bytes, takes each wave's tables);
 // prepare_decode must have run for (h, C, a.K)
-hipError_t launch_decode(int h, int C, const DecArgs& a, int grid, int waves, hipStream_t s);
+hipError_t launch_decode(int h, int C, const DecArgs& a, int grid, int waves, size_t lds, hipStream_t s);
 // ancestral sampling with the decoder's schedule (DecArgs: in, in_off, status
 // and sym_dump unused; every image descriptor carries its seed)
-hipError_t launch_sample(int h, int C, const DecArgs& a, int grid, int waves, hipStream_t s);
+hipError_t launch_sample(int h, int C, const DecArgs& a, int grid, int waves, size_t lds, hipStream_t s);
 // per-image FP64 sums of per-pixel bits, in a fixed order (partials: n_img
 // x REDUCE_PARTS doubles of scratch)
 constexpr int REDUCE_PARTS = 64;

@@ -34,11 +34,9 @@ constexpr int WIN_PLANES = 2 * 3 * RING_COLS;
 // is input k = 16 j + a of the pixel. What its place in the window has besides
 // the step and the pixel's row is the lane's for good.
 template <int H_>
-constexpr int quad_inputs() { return (4 * conv_chunks(H_) + 15) / 16; }
-template <int H_>
-NXD void quad_offsets(int (&off)[quad_inputs<H_>()], int rows, int lane) {
+NXD void quad_offsets(int (&off)[quad_inputs(H_)], int rows, int lane) {
 #pragma unroll
-  for (int j = 0; j < quad_inputs<H_>(); ++j) {
+  for (int j = 0; j < quad_inputs(H_); ++j) {
     const int k = min(16 * j + (lane >> 2), 4 * conv_chunks(H_) - 1);
     const int dy = min(k / (3 * (2 * H_ + 1)), H_);
     off[j] = (k - 3 * H_ * dy) * rows + dy;
@@ -46,14 +44,14 @@ NXD void quad_offsets(int (&off)[quad_inputs<H_>()], int rows, int lane) {
 }
 // contexts of the wave's pixels at step t, i the window row of the lane's
 template <int H_>
-NXD void quad_gather(float (&cx)[quad_inputs<H_>()], const int (&off)[quad_inputs<H_>()], const int16_t* win, int rows,
+NXD void quad_gather(float (&cx)[quad_inputs(H_)], const int (&off)[quad_inputs(H_)], const int16_t* win, int rows,
                      int t, int i) {
   const int16_t* b = win + 3 * ((t - H_ * (H_ + 2)) & (RING_COLS - 1)) * rows + i;
-  int raw[quad_inputs<H_>()];
+  int raw[quad_inputs(H_)];
 #pragma unroll
-  for (int j = 0; j < quad_inputs<H_>(); ++j) raw[j] = b[off[j]];
+  for (int j = 0; j < quad_inputs(H_); ++j) raw[j] = b[off[j]];
 #pragma unroll
-  for (int j = 0; j < quad_inputs<H_>(); ++j) cx[j] = (float)raw[j] * (1.0f / 255.0f);
+  for (int j = 0; j < quad_inputs(H_); ++j) cx[j] = (float)raw[j] * (1.0f / 255.0f);
 }
 
 // both copies of plane `plane` (of column t), row r
@@ -63,143 +61,7 @@ NXD void win_put(int16_t* win, int rows, int t, int ch, int r, int v) {
   b[3 * RING_COLS * rows] = (int16_t)v;
 }
 
-// ------------------------------------------------------------------ network
-// The network of a wave's four pixels. v_mfma_f32_4x4x1f32 adds 16 outer
-// products (blocks) of 4 x 4; with the activations as its A operand, one
-// block's four pixels broadcast to all (cbsz 4, block abid), and the weights
-// as B, it is one input k of 64 outputs: lane l has output l, register v pixel
-// v, and A's block abid has input k of pixel r in lane 4 abid + r. Inputs are
-// added in the order k = 0, 1, ..., the order, and with the roundings, of the
-// 16x16x4 form (each a chain of fused multiply-adds). A layer's outputs become the
-// next one's A operand by a 4 x 4 transpose within each four lanes. (C < 64:
-// the lanes past C repeat the others.) No value leaves the wave: split by
-// output tiles instead, a layer is 16 instructions of 32 cycles and not 64 of
-// 12.5 (each waits for the last), but six exchanges through LDS a group cost
-// 600 cycles each. Model B's network: 7.3 thousand cycles a group so split,
-// about 6 so; one 1024 x 1024 image with a stream per row, with the link wave below: 34.6 -> 29.9 ms.
-// Head row 64 i + l goes to hb[pixel * HB_STRIDE + 64 i + l].
 constexpr int TEAM_WAVES = ROW_WAVES;
-constexpr int HB_STRIDE = 132;
-template <int A>
-NXD f4 quad_mfma(float act, float w, f4 d) { return __builtin_amdgcn_mfma_f32_4x4x1f32(act, w, d, 4, A, 0); }
-
-template <int CTRL>
-NXD float quad_dpp(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
-}
-// x[j] of lane 4 a + r = u[r] of lane 4 a + j
-NXD f4 quad_transpose(const f4& u, int lane) {
-  const bool o0 = lane & 1, o1 = lane & 2;
-  // (all lanes exchange, then each picks: no branch around an exchange)
-  f4 e, y, x;
-#pragma unroll
-  for (int c = 0; c < 4; ++c) e[c] = quad_dpp<0xB1>(u[c ^ 1]);
-#pragma unroll
-  for (int c = 0; c < 4; ++c) y[c] = o0 == ((c & 1) != 0) ? u[c] : e[c];
-#pragma unroll
-  for (int c = 0; c < 4; ++c) e[c] = quad_dpp<0x4E>(y[c ^ 2]);
-#pragma unroll
-  for (int c = 0; c < 4; ++c) x[c] = o1 == ((c & 2) != 0) ? y[c] : e[c];
-  return x;
-}
-NXD f4 quad_act(const f4& a, int lane) {
-  f4 u;
-#pragma unroll
-  for (int v = 0; v < 4; ++v) u[v] = xelu(a[v]);
-  return quad_transpose(u, lane);
-}
-NXD f4 splat(float b) { return f4{b, b, b, b}; }
-
-// The weights of 16 inputs, N outputs a lane (rows `stride` floats apart): four
-// 16-byte reads of LDS each. They are issued a chunk of 16 inputs ahead of
-// their use (the barrier to scheduling keeps them there): read where they are used, they cost
-// a wait of about 130 cycles in every chunk of 200.
-template <int N>
-struct QuadW {
-  f4 v[4][N];
-  NXD void load(const float* w, int stride) {
-#pragma unroll
-    for (int g = 0; g < 4; ++g)
-#pragma unroll
-      for (int n = 0; n < N; ++n) v[g][n] = *(const f4*)(w + n * stride + 64 * g);
-    __builtin_amdgcn_sched_barrier(0);
-  }
-};
-// 16 inputs of block 4 CT's lanes on: chunk (ct, q) of the 16x16x4 form holds
-// inputs 16 ct + 4 g + q, g = 0 .. 3, and their order is the order here
-template <int CT, int N, int Q = 0, int G = 0>
-NXD void quad_chunk(const QuadW<N>& w, const f4& x, f4 (&d)[N]) {
-#pragma unroll
-  for (int n = 0; n < N; ++n) d[n] = quad_mfma<4 * CT + G>(x[Q], w.v[G][n][Q], d[n]);
-  if constexpr (G < 3) quad_chunk<CT, N, Q, G + 1>(w, x, d);
-  else if constexpr (Q < 3) quad_chunk<CT, N, Q + 1, 0>(w, x, d);
-}
-// a layer of 16 CTS inputs; w[0] holds its first chunk, and in the end what
-// `next` points at
-template <int CTS, int N, int CT = 0>
-NXD void quad_layer(const float* wl, int stride, const float* next, const f4& x, QuadW<N> (&w)[2], f4 (&d)[N]) {
-  w[(CT + 1) & 1].load(CT + 1 < CTS ? wl + (CT + 1) * 256 : next, stride);
-  quad_chunk<CT, N>(w[CT & 1], x, d);
-  if constexpr (CT + 1 < CTS) quad_layer<CTS, N, CT + 1>(wl, stride, next, x, w, d);
-  else if constexpr (CTS & 1) w[0] = w[1];
-}
-// inputs 16 kq .. of the first layer (there in ascending order)
-template <int H_, int KQ_, int Q = 0, int G = 0>
-NXD void quad_first_chunk(const QuadW<1>& w, float cx, f4& d) {
-  if constexpr (4 * KQ_ + Q < conv_chunks(H_)) {
-    d = quad_mfma<4 * Q + G>(cx, w.v[G][0][Q], d);
-    if constexpr (G < 3) quad_first_chunk<H_, KQ_, Q, G + 1>(w, cx, d);
-    else if constexpr (Q < 3) quad_first_chunk<H_, KQ_, Q + 1, 0>(w, cx, d);
-  }
-}
-template <int H_, int KQ_ = 0>
-NXD void quad_first(const float* wl, const float* next, const float (&cx)[quad_inputs<H_>()], QuadW<1> (&w)[2], f4& d) {
-  constexpr int KQ = conv_quads(H_), P = (KQ_ + KQ) & 1;  // the last chunk in w[1]
-  w[P ^ 1].load(KQ_ + 1 < KQ ? wl + (KQ_ + 1) * 256 : next, 0);
-  quad_first_chunk<H_, KQ_>(w[P], cx[KQ_], d);
-  if constexpr (KQ_ + 1 < KQ) quad_first<H_, KQ_ + 1>(wl, next, cx, w, d);
-}
-
-template <int H_, int C_>
-NXD void net_quad(const float* __restrict__ w, int nb, const float (&cx)[quad_inputs<H_>()], float* hb, int lane) {
-  constexpr int MT = C_ / 16;
-  const WeightLayout L = weight_layout(H_, C_, 0);
-  const int l = lane & (C_ - 1), r16 = lane & 15;
-  const int layer_stride = MT * MT * 256;
-  const float* bias_conv = w + L.head + HEAD_TILES * MT * 256 + 2 * nb * layer_stride;
-  const float* bias_head = bias_conv + C_ + 2 * nb * C_;
-  const float* wl = w + L.layer0 + ((l >> 4) * MT * 64 + r16) * 4;
-  const float* bl = bias_conv + C_ + l;
-  const float* wc = w + ((l >> 4) * conv_quads(H_) * 64 + r16) * 4;
-  QuadW<1> q[2];
-  q[conv_quads(H_) & 1].load(wc, 0);
-  f4 a[1] = {splat(bias_conv[l])}, z[1];
-  quad_first<H_>(wc, wl, cx, q, a[0]);
-  for (int b = 0; b < nb; ++b) {
-    z[0] = splat(bl[0]);
-    quad_layer<MT, 1>(wl, 0, wl + layer_stride, quad_act(a[0], lane), q, z);
-    const f4 x = quad_act(z[0], lane);
-    z[0] = splat(bl[C_]);
-    wl += layer_stride;
-    quad_layer<MT, 1>(wl, 0, wl + layer_stride, x, q, z);
-    a[0] = a[0] + z[0];
-    wl += layer_stride;
-    bl += 2 * C_;
-  }
-  f4 h[2] = {splat(bias_head[lane]), splat(bias_head[64 + lane])};
-  const float* w_head = w + L.layer0 + 2 * nb * layer_stride + ((lane >> 4) * MT * 64 + r16) * 4;
-  QuadW<2> qh[2];
-  qh[0].load(w_head, 4 * MT * 256);
-  quad_layer<MT, 2>(w_head, 4 * MT * 256, w_head, quad_act(a[0], lane), qh, h);
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    hb[v * HB_STRIDE + lane] = h[0][v];
-    hb[v * HB_STRIDE + 64 + lane] = h[1][v];
-  }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // ------------------------------------------------------------------ mixture, 16 lanes per pixel
 template <int M>
@@ -357,7 +219,7 @@ __global__ void __launch_bounds__(2 * TEAM_WAVES * 64) k_decode_team(DecArgs A) 
   const int v4 = (w4 + 2 * team) & (TEAM_WAVES - 1);
   auto slot_of = [&](int q) { return KIND == POPS_ROWS && K == 8 ? 2 * v4 + (q & 1) + 8 * (q >> 1) : 4 * v4 + q; };
   const int slot = slot_of(s), nslot = slot_of(lane & 3);  // the mixture's pixel, the network's
-  int off[quad_inputs<H_>()];
+  int off[quad_inputs(H_)];
   quad_offsets<H_>(off, rows, lane);
   // barriers of one group
   constexpr int n_bar = 1 + (KIND == POPS_SERIAL ? 6 : 0);
@@ -518,9 +380,9 @@ __global__ void __launch_bounds__(2 * TEAM_WAVES * 64) k_decode_team(DecArgs A) 
       Mix16 M;
       uint32_t sl[3] = {0u, 0u, 0u};
       if (busy) {
-        float cx[quad_inputs<H_>()];
-        quad_gather<H_>(cx, off, win, rows, gi, min(ts + nslot, Hl - 1));
-        net_quad<H_, C_>(lds_weights(wts), A.nb, cx, hb, lane);
+        float cx[1][quad_inputs(H_)];
+        quad_gather<H_>(cx[0], off, win, rows, gi, min(ts + nslot, Hl - 1));
+        net_quad<H_, C_, 1>(lds_weights(wts), A.nb, cx, hb, lane);
         mix_prep16(hb + s * HB_STRIDE, m, M);
         if constexpr (KIND == POPS_SAMPLE) sample_slots(seed, W, y0 + i, x0 + j, sl);
       }
@@ -792,7 +654,7 @@ __device__ void decode_band(const DecArgs& A, const float* w, float* hbs, int16_
     uint32_t* dump = A.sym_dump ? A.sym_dump + D.px_base * 3 : nullptr;
     const bool live = m < 10;
     const int i = r0 + pp;
-    int off[quad_inputs<H_>()];
+    int off[quad_inputs(H_)];
     quad_offsets<H_>(off, rows, lane);
     for (int t = t_lo; t <= t_hi; ++t) {
       __syncthreads();
@@ -801,9 +663,9 @@ __device__ void decode_band(const DecArgs& A, const float* w, float* hbs, int16_
       int xv[3] = {0, 0, 0};
       if (__ballot(act) != 0ull) {
         {
-          float cx[quad_inputs<H_>()];
-          quad_gather<H_>(cx, off, win, rows, t, 4 * wave + (lane & 3));
-          net_quad<H_, C_>(lds_weights(w), A.nb, cx, hb, lane);
+          float cx[1][quad_inputs(H_)];
+          quad_gather<H_>(cx[0], off, win, rows, t, 4 * wave + (lane & 3));
+          net_quad<H_, C_, 1>(lds_weights(w), A.nb, cx, hb, lane);
         }
         Mix16 M;
         mix_prep16(hb + s * HB_STRIDE, m, M);
