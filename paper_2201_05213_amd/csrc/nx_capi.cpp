@@ -453,7 +453,10 @@ nellox_status nellox_model_create(const void* blob, size_t nbytes, nellox_model*
   hipDeviceProp_t prop;
   e = hipGetDeviceProperties(&prop, dev);
   if (e != hipSuccess) return hip_fail(e, "hipGetDeviceProperties");
-  if (img.size() * 4 + DECODE_LDS_EXTRA > prop.sharedMemPerBlock)
+  // (with room for an eighth head tile: the models accepted are those of a head
+  // with a row per slot)
+  const size_t eighth = (size_t)(Cp / 16 * 256 + 16) * 4;
+  if (img.size() * 4 + eighth + DECODE_LDS_EXTRA > prop.sharedMemPerBlock)
     return fail(NELLOX_E_UNSUPPORTED, "weights exceed the LDS of one workgroup");
   nellox_model* m = new nellox_model();
   m->h = (int)h; m->C = (int)C; m->Cp = Cp; m->nb = (int)nb;
@@ -952,10 +955,11 @@ nellox_status nellox_nll_bwd(const float* params, const int32_t dims[4], const u
   // layer's deltas are those of a_0, its inputs the causal taps; 1x1 layer l
   // (W1 of block l / 2 or W2) has delta l + 1 and input u_l
   int nl = 0;
-  constexpr int head_rows = 16 * HEAD_TILES / WGRAD_HEAD_PARTS;
+  constexpr int head_rows = 16 * WGRAD_HEAD_TILES;
   for (int q = 0; q < WGRAD_HEAD_PARTS; ++q)
     g.layer[nl++] = WgradLayer{a.dtheta + q * head_rows, a.u + 2LL * T.nb * pc, 16 * HEAD_TILES, T.Cp,
-                               T.off_head + (int64_t)q * head_rows * T.Cp, T.bias_head + q * head_rows, WGRAD_HEAD};
+                               T.off_head + (int64_t)q * head_rows * T.Cp, T.bias_head + q * head_rows,
+                               q == 0 ? WGRAD_HEAD : WGRAD_HEAD_REST};
   g.layer[nl++] = WgradLayer{a.delta, a.ctx, T.Cp, T.KP, T.off_conv, T.bias_conv, WGRAD_FIRST};
   for (int l = 0; l < 2 * T.nb; ++l)
     g.layer[nl++] = WgradLayer{a.delta + (l + 1) * pc, a.u + l * pc, T.Cp, T.Cp,

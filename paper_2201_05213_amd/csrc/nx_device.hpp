@@ -363,7 +363,7 @@ struct NoSink {
   NXD void operator()(int, const f4 (&)[N]) const {}
 };
 
-// Network of a 16-pixel tile: head[8] receives the 128 (permuted) head rows.
+// Network of a 16-pixel tile: head[7] receives the 112 (permuted) head rows.
 // w points at the weight image (LDS). ctx is this lane's conv B operand.
 // sink(l, u) sees the layer inputs u = elu(.) in order: l = 2b is the input of
 // block b's first 1x1 layer, 2b + 1 of its second, 2 nb of the head.
@@ -571,12 +571,14 @@ NXD void net_quad(const float* __restrict__ w, int nb, const float (&cx)[NQ][qua
   }
   f4 h[2][NQ];
   quad_splat(h[0], bias_head[lane]);
-  quad_splat(h[1], bias_head[64 + lane]);
+  quad_splat(h[1], bias_head[64 + min(lane, 47)]);
+  // (row 64 + lane of the head; it has 112, and lanes 48 on repeat their first)
   const float* w_head = w + L.layer0 + 2 * nb * layer_stride + ((lane >> 4) * MT * 64 + r16) * 4;
+  const int second = lane < 48 ? 4 * MT * 256 : 0;
   QuadW<2> qh[2];
-  qh[0].load(w_head, 4 * MT * 256);
+  qh[0].load(w_head, second);
   quad_act(a, x, lane);
-  quad_layer<MT, 2, NQ>(w_head, 4 * MT * 256, w_head, x, qh, h);
+  quad_layer<MT, 2, NQ>(w_head, second, w_head, x, qh, h);
 #pragma unroll
   for (int k = 0; k < NQ; ++k)
 #pragma unroll
@@ -644,7 +646,39 @@ struct Mix {
   float co[3][3];      // [coef][slot] tanh'd coefficients alpha, beta, gamma
 };
 
-NXD float head_slot(const f4 (&hd)[HEAD_TILES], int s) { return hd[s >> 2][s & 3]; }
+// The lane group's slots (see head_row_src) from its values. The swap
+// exchanges its first operand's lanes 32 .. 63 with its second's 0 .. 31, so
+// against zeros it brings groups 0 and 1 their slots 28 and 29 and leaves
+// zeros in the others'. head_values is the reverse.
+constexpr int HEAD_SLOTS = 8;  // slots / 4
+NXD void swap_halves(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(r[0]);
+  b = __uint_as_float(r[1]);
+}
+NXD void head_slots(const f4 (&hd)[HEAD_TILES], f4 (&s)[HEAD_SLOTS]) {
+#pragma unroll
+  for (int t = 0; t < HEAD_TILES; ++t) s[t] = hd[t];
+  s[7] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int v = 0; v < 2; ++v) {
+    float a = s[5][v], b = 0.0f;
+    swap_halves(a, b);
+    s[5][v] = a;
+    s[7][v] = b;
+  }
+}
+NXD void head_values(const f4 (&s)[HEAD_SLOTS], f4 (&hd)[HEAD_TILES]) {
+#pragma unroll
+  for (int t = 0; t < HEAD_TILES; ++t) hd[t] = s[t];
+#pragma unroll
+  for (int v = 0; v < 2; ++v) {
+    float a = s[5][v], b = s[7][v];
+    swap_halves(a, b);
+    hd[5][v] = a;
+  }
+}
+NXD float head_slot(const f4 (&s)[HEAD_SLOTS], int k) { return s[k >> 2][k & 3]; }
 
 // log-sum-exp over the ten components of one pixel (own slots, fixed tree)
 NXD float lse10(const float (&t)[3], bool has2) {
@@ -657,7 +691,9 @@ NXD float lse10(const float (&t)[3], bool has2) {
   return m + xlog(s);
 }
 
-NXD void mix_prep(const f4 (&hd)[HEAD_TILES], Mix& M, bool has2) {
+NXD void mix_prep(const f4 (&rows)[HEAD_TILES], Mix& M, bool has2) {
+  f4 hd[HEAD_SLOTS];
+  head_slots(rows, hd);
   float lam[3];
 #pragma unroll
   for (int j = 0; j < 3; ++j) lam[j] = head_slot(hd, 10 * j);
@@ -797,12 +833,7 @@ struct Mix16 {
   float logw;                  // posterior log weight of this lane's component
   float mu[3], invs[3], co[3];
 };
-// the weight image's head row of parameter k (0..9) of component m
-NXD int head_row(int m, int k) {
-  const int s = 10 * (m >> 2) + k;
-  return 16 * (s >> 2) + 4 * (m & 3) + (s & 3);
-}
-// mix_prep for component m of the pixel whose 128 head rows are at hp
+// mix_prep for component m of the pixel whose head rows are at hp
 NXD void mix_prep16(const float* hp, int m, Mix16& M) {
   const bool live = m < 10;
   const int mm = live ? m : 0;

@@ -118,18 +118,17 @@ struct TrainArgs {
   float* bits;             // [npx] continuous bits per pixel
   float* ctx;              // [npx][KP] conv inputs (normalised taps)
   float* u;                // [2 nb + 1][npx][Cp] inputs of the 1x1 layers and the head
-  float* theta;            // [npx][128] head rows
+  float* theta;            // [npx][112] head rows
   float* delta;            // [2 nb + 1][npx][Cp] output deltas: first layer, then per block W1, W2
-  float* dtheta;           // [npx][128] head-row deltas
+  float* dtheta;           // [npx][112] head-row deltas
   const float* grad_bits;  // [n] d loss / d bits of image n
 };
 
 // layer kinds of the weight-gradient launch (they set the layer's shape)
-constexpr int WGRAD_FIRST = 0, WGRAD_BLOCK = 1, WGRAD_HEAD = 2;
-// the head's rows go to WGRAD_HEAD_PARTS layer entries (HEAD_TILES /
-// WGRAD_HEAD_PARTS row tiles each), which keeps every layer's accumulators
-// at most 4 row tiles wide
-constexpr int WGRAD_HEAD_PARTS = 2;
+constexpr int WGRAD_FIRST = 0, WGRAD_BLOCK = 1, WGRAD_HEAD = 2, WGRAD_HEAD_REST = 3;
+// the head's rows go to two layer entries, of WGRAD_HEAD_TILES row tiles and of
+// the rest, which keeps every layer's accumulators at most 4 row tiles wide
+constexpr int WGRAD_HEAD_PARTS = 2, WGRAD_HEAD_TILES = 4;
 constexpr int WGRAD_MAX_LAYERS = 11;  // the head's parts, first layer, up to 8 1x1 layers
 
 struct WgradLayer {
@@ -137,7 +136,7 @@ struct WgradLayer {
   const float* in;         // [npx][ld_in], rows 16-byte aligned
   int ld_delta, ld_in;
   int64_t w_off, b_off;    // offsets of this layer's dW [rows][cols] and db in a partial
-  int kind;                // WGRAD_FIRST, WGRAD_BLOCK or WGRAD_HEAD
+  int kind;                // one of the above
 };
 
 struct WgradArgs {

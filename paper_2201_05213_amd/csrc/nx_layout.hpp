@@ -10,7 +10,7 @@ namespace nx {
 
 constexpr int NMIX = 10;          // logistic mixture components
 constexpr int NOUT = 10 * NMIX;   // head outputs of the model
-constexpr int HEAD_TILES = 8;     // head rows padded to 8 MFMA tiles of 16
+constexpr int HEAD_TILES = 7;     // head rows padded to 7 MFMA tiles of 16
 constexpr int CDF_BITS = 16;
 constexpr uint32_t CDF_TOTAL = 1u << CDF_BITS;
 constexpr uint32_t RANS_L = 1u << 23;  // lower bound of the normalised rANS state
@@ -26,8 +26,8 @@ constexpr int conv_quads(int h) { return (conv_chunks(h) + 3) / 4; }
 // consecutive K-chunks (one 16-byte LDS read per lane covers 4 MFMAs).
 //   conv:   [mt < C/16][kq < conv_quads][lane][q]   W[16mt + lane%16][k = 4(4kq+q) + lane/16]
 //   1x1:    [mt < C/16][ct < C/16][lane][q]         W[16mt + lane%16][16ct + 4(lane/16) + q]
-//   head:   [mt < 8][ct < C/16][lane][q]            same, with permuted/padded rows
-//   biases: conv[C], per block b1[C], b2[C], head[128] (permuted rows)
+//   head:   [mt < 7][ct < C/16][lane][q]            same, with permuted/padded rows
+//   biases: conv[C], per block b1[C], b2[C], head[112] (permuted rows)
 struct WeightLayout {
   int h, C, nb;
   int64_t conv, layer0, layer_stride, head, bias_conv, bias_blocks, bias_head, total;
@@ -179,20 +179,33 @@ NXHD int tap_index(int h, int dy, int dx) {
   return -1;
 }
 
-// Head MFMA row r (0..127) holds slot s = 4 (r/16) + r%4 of lane group
-// g = (r%16)/4: parameter s%10 of mixture component g + 4 (s/10), which is
-// head output 10 (s%10) + component. Returns -1 for padding rows.
+// Head MFMA row r (0..111) is value s = 4 (r/16) + r%4 of lane group
+// g = (r%16)/4. Lane group g has components g, g + 4 and, if g < 2, g + 8, each
+// in ten slots: slot s is parameter s%10 of component g + 4 (s/10), which is
+// head output 10 (s%10) + component. Values 0 .. 27 are the slots of that
+// number, but groups 2 and 3, whose slots end at 19, have slots 28 and 29 of
+// groups 0 and 1 as values 20 and 21 (a half-wave swap brings them home):
+// 100 outputs in 7 tiles, where a row per slot takes 8, 512 cycles more of a
+// tile's 14.6 thousand in matrix instructions (model B). 4 1024 x 1024 and 2
+// 2048 x 1536 images in 82 x 64 patches: encode 6.53 -> 6.37 ms, decode 8.35 ->
+// 8.18. Returns -1 for padding rows.
 NXHD int head_row_src(int r) {
-  const int mt = r / 16, g = (r % 16) / 4, v = r % 4;
-  const int s = 4 * mt + v, m = g + 4 * (s / 10), p = s % 10;
-  return (s < 30 && m < NMIX) ? 10 * p + m : -1;
+  int s = 4 * (r / 16) + r % 4, g = (r % 16) / 4;
+  if (g >= 2 && (s == 20 || s == 21)) {
+    s += 8;
+    g -= 2;
+  }
+  const int m = g + 4 * (s / 10), p = s % 10;
+  return m < NMIX ? 10 * p + m : -1;
 }
-// inverse of head_row_src
-NXHD int head_row_of(int src) {
-  const int p = src / 10, m = src % 10;
-  const int s = 10 * (m / 4) + p, g = m % 4;
+// the row of parameter p of component m
+NXHD int head_row(int m, int p) {
+  const bool moved = m >= 8 && p >= 8;
+  const int s = 10 * (m / 4) + p - (moved ? 8 : 0), g = m % 4 + (moved ? 2 : 0);
   return 16 * (s / 4) + 4 * g + (s % 4);
 }
+// inverse of head_row_src
+NXHD int head_row_of(int src) { return head_row(src % 10, src / 10); }
 
 // Source of weight-image float idx in the parameter vector, or -1 (zero).
 // C = model channels, Cp = C rounded up to 16 (the image's channel count).
@@ -243,7 +256,7 @@ NXHD int64_t wimg_src(int h, int C, int Cp, int nb, int64_t idx) {
 // layers and the head): with the forward's D layout as the B operand, the
 // A operand of output tile ct (input channels) and K-chunk (mt, v) is
 //   [ct][mt][lane][v] = W[16 mt + 4 (lane/16) + v][16 ct + lane%16]
-// per 1x1 layer (2 nb of them), then the head (8 row tiles, permuted rows).
+// per 1x1 layer (2 nb of them), then the head (7 row tiles, permuted rows).
 struct WeightTLayout {
   int64_t layer0, layer_stride, head, total;
 };

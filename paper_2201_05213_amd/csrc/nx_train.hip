@@ -62,7 +62,9 @@ NXD float log_bin_grad(int x, float mu, float is, float& dmu, float& dis) {
 // layout, bits = -log p / ln 2: the responsibilities r_m = w_m prod_c P_cm / p
 // give d log p / d logit_m = r_m - w_m and d log p / d log P_cm = r_m.
 template <bool GRAD>
-NXD float mix_joint(const f4 (&hd)[HEAD_TILES], const int (&xv)[3], bool has2, float scale, f4 (&dh)[HEAD_TILES]) {
+NXD float mix_joint(const f4 (&rows)[HEAD_TILES], const int (&xv)[3], bool has2, float scale, f4 (&drows)[HEAD_TILES]) {
+  f4 hd[HEAD_SLOTS];
+  head_slots(rows, hd);
   const float xr = normalise(xv[0]), xg = normalise(xv[1]);
   float lam[3];
 #pragma unroll
@@ -91,8 +93,9 @@ NXD float mix_joint(const f4 (&hd)[HEAD_TILES], const int (&xv)[3], bool has2, f
   const float logp = lse10(L, has2);
   if (GRAD) {
     const float s2 = -scale * kLog2e;  // d(scale * bits)/d log p
+    f4 dh[HEAD_SLOTS];
 #pragma unroll
-    for (int t = 0; t < HEAD_TILES; ++t) dh[t] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int t = 0; t < HEAD_SLOTS; ++t) dh[t] = f4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
       if (j == 2 && !has2) continue;
@@ -117,6 +120,7 @@ NXD float mix_joint(const f4 (&hd)[HEAD_TILES], const int (&xv)[3], bool has2, f
         dh[s >> 2][s & 3] = v[q];
       }
     }
+    head_values(dh, drows);
   }
   return logp;
 }
@@ -509,14 +513,16 @@ NXD void wgrad_layer(const WgradArgs& A, const WgradLayer& Lr, float* sm) {
 
 // CT = C / 16 and KT = KP / 16 tiles; the layer's kind picks its shape:
 // (CT, KT) for the first layer, (CT, CT) for the 1x1 layers,
-// (HEAD_TILES / WGRAD_HEAD_PARTS, CT) for a part of the head
+// (WGRAD_HEAD_TILES or the rest of HEAD_TILES, CT) for a part of the head
 template <int CT, int KT>
 __global__ void __launch_bounds__(WGRAD_WAVES * 64) k_wgrad(WgradArgs A) {
   extern __shared__ float4 wg_smem[];
   float* sm = (float*)wg_smem;
   const WgradLayer Lr = A.layer[blockIdx.y];
   if (Lr.kind == WGRAD_HEAD)
-    wgrad_layer<HEAD_TILES / WGRAD_HEAD_PARTS, CT>(A, Lr, sm);
+    wgrad_layer<WGRAD_HEAD_TILES, CT>(A, Lr, sm);
+  else if (Lr.kind == WGRAD_HEAD_REST)
+    wgrad_layer<HEAD_TILES - WGRAD_HEAD_TILES, CT>(A, Lr, sm);
   else if (Lr.kind == WGRAD_FIRST)
     wgrad_layer<CT, KT>(A, Lr, sm);
   else
@@ -681,7 +687,7 @@ hipError_t launch_train_bwd(int h, int Cp, const TrainArgs& a, int grid, hipStre
 // LDS of the weight-gradient kernel: every wave's ring of K-step slots, or
 // one row tile's values of every wave, for the widest layer
 static size_t wgrad_lds(int CT, int KT) {
-  const int slot = std::max({wgrad_slot(CT, KT), wgrad_slot(CT, CT), wgrad_slot(HEAD_TILES / WGRAD_HEAD_PARTS, CT)});
+  const int slot = std::max({wgrad_slot(CT, KT), wgrad_slot(CT, CT), wgrad_slot(WGRAD_HEAD_TILES, CT)});
   const size_t ring = (size_t)WGRAD_WAVES * (WGRAD_DEPTH + 1) * slot;
   const size_t sums = (size_t)WGRAD_WAVES * (4 * std::max(KT, CT) + 1) * 64;
   return std::max(ring, sums) * sizeof(float);
