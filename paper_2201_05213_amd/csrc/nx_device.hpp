@@ -656,6 +656,12 @@ NXD void swap_halves(float& a, float& b) {
   a = __uint_as_float(r[0]);
   b = __uint_as_float(r[1]);
 }
+// a's lane rows 1 and 3 with b's 0 and 2
+NXD void swap_rows(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(r[0]);
+  b = __uint_as_float(r[1]);
+}
 NXD void head_slots(const f4 (&hd)[HEAD_TILES], f4 (&s)[HEAD_SLOTS]) {
 #pragma unroll
   for (int t = 0; t < HEAD_TILES; ++t) s[t] = hd[t];
