@@ -73,7 +73,9 @@ typedef struct {
                          sheared layout (ShearLoC, Sec. 3.1, Algorithm 2): the coded order
                          and the containers of 2 are those of 1; a decoder with order 2
                          gathers each pixel's context from a window of the lane's
-                         sheared canvas, where every step is one column */
+                         sheared canvas, where every step is one column (with at
+                         most two lanes per CU orders 1 and 2 decode alike, from
+                         such a window in LDS) */
   int32_t patch_h;    /* patch rows; <= 0 or >= H: whole image */
   int32_t patch_w;    /* patch columns; <= 0 or >= W: whole image */
   int32_t interleave; /* rANS states per lane: 0 or 1 = one; 2, 4, 8 or 16 (wavefront
@@ -189,7 +191,7 @@ typedef struct {
   int64_t desc_offset;          /* byte offset of the descriptors in the workspace */
   int64_t counter_offset;       /* byte offset of the lane-queue counter */
   int64_t ring_offset;          /* order 2: byte offset of the per-wave sheared context rings */
-  int64_t ring_rows;            /* order 2: rows of a ring (tallest lane + h, padded) */
+  int64_t ring_rows;            /* orders 1 and 2: rows of a context window (tallest lane + h, padded) */
   int64_t n_bands;              /* row streams: bands of 16 lane rows (the launch's work items) */
   int64_t progress_offset;      /* row streams: byte offset of the per-band progress counters */
   int64_t band_order_offset;    /* row streams: byte offset of the bands' queue order (0: image order) */

@@ -1389,7 +1389,7 @@ static hipError_t pass_t(const PassArgs& a, int grid, hipStream_t s) {
 // A wave's LDS: pivot and mixture tables, or a head table of as many pixels
 // (a multiple of 4, at most 12) as the LDS left by the weights gives each
 // wave. Groups of at most that many pixels take net_quad, at 3,650 cycles of
-// matrix instructions per four pixels (model B) against 14,600 for a tile.
+// matrix instructions per four pixels (model B) against 14,100 for a tile.
 // Measured with the sheared window's shorter gather, 4 1024 x 1024 and 2
 // 2048 x 1536 images in 82 x 64 patches (96 of a patch's 388 steps have at
 // most 12 rows): 8.71 -> 8.35 ms.

@@ -186,7 +186,7 @@ NXHD int tap_index(int h, int dy, int dx) {
 // number, but groups 2 and 3, whose slots end at 19, have slots 28 and 29 of
 // groups 0 and 1 as values 20 and 21 (a half-wave swap brings them home):
 // 100 outputs in 7 tiles, where a row per slot takes 8, 512 cycles more of a
-// tile's 14.6 thousand in matrix instructions (model B). 4 1024 x 1024 and 2
+// tile's 14.1 thousand in matrix instructions (model B). 4 1024 x 1024 and 2
 // 2048 x 1536 images in 82 x 64 patches: encode 6.53 -> 6.37 ms, decode 8.35 ->
 // 8.18. Returns -1 for padding rows.
 NXHD int head_row_src(int r) {
