@@ -71,20 +71,28 @@ NXD float xtanh(float x) {
   return __builtin_copysignf(t, x);
 }
 
+// The larger of a and b, the other one where one is NaN (as fmaxf): their
+// median with infinity (a value the compiler does not see: it would make it a
+// maximum, prefaced with a quieting v_max of each operand that comes from a
+// lane exchange, a load or a matrix instruction; about 30 of the 1,250 vector
+// instructions of a tile of the pass: 64 images of 64 to 320 wide, model C,
+// encoded in 942 -> 929 us, their code lengths, model B, in 1.36 -> 1.347 ms).
+NXD float xmax(float a, float b) {
+  float inf = INFINITY;
+  asm("" : "+s"(inf));
+  return __builtin_amdgcn_fmed3f(a, b, inf);
+}
+
 // ELU with exp(x) - 1 from the hardware exp2 for x <= 0: the rounding of
 // x log2(e) costs a relative error of at most |x| 2^-24 ln2 in exp(x), i.e.
 // an absolute error below 3e-8 in the activation. 1 - exp(x), clamped to
 // [0, 1] by the subtraction's output modifier, is 0 for x > 0 and its negative
 // is the activation for x <= 0, where exp(x) - 1 >= x; so the larger of x and
 // that is the activation (x itself where rounding put it above, |x| < 2^-23).
-// The maximum is a median with infinity (a value the compiler does not see:
-// it would make it a maximum, prefaced with a quieting v_max of x): 4
-// instructions where min, max and their quieting took 6.
+// 4 instructions where min, max and their quieting took 6.
 NXD float xelu(float x) {
-  float inf = INFINITY;
-  asm("" : "+s"(inf));
   const float c = __builtin_amdgcn_fmed3f(1.0f - __builtin_amdgcn_exp2f(x * kLog2e), 0.0f, 1.0f);
-  return __builtin_amdgcn_fmed3f(x, -c, inf);
+  return xmax(x, -c);
 }
 
 // logistic sigmoid: monotone non-decreasing in z because the hardware exp2
@@ -125,10 +133,10 @@ NXD float grp_sum(float v) {
 NXD float grp_max(float v) {
   const uint32_t u = __float_as_uint(v);
   const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  const float s = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  const float s = xmax(__uint_as_float(r[0]), __uint_as_float(r[1]));
   const uint32_t w = __float_as_uint(s);
   const auto q = __builtin_amdgcn_permlane32_swap(w, w, false, false);
-  return fmaxf(__uint_as_float(q[0]), __uint_as_float(q[1]));
+  return xmax(__uint_as_float(q[0]), __uint_as_float(q[1]));
 }
 // ------------------------------------------------------------------ gather
 // Causal context of pixel (i, j) of a lane (a rect of Hl x Wl pixels at (y0, x0)
@@ -686,13 +694,13 @@ NXD void head_values(const f4 (&s)[HEAD_SLOTS], f4 (&hd)[HEAD_TILES]) {
 }
 NXD float head_slot(const f4 (&s)[HEAD_SLOTS], int k) { return s[k >> 2][k & 3]; }
 
-// log-sum-exp over the ten components of one pixel (own slots, fixed tree)
-NXD float lse10(const float (&t)[3], bool has2) {
-  float m = fmaxf(t[0], t[1]);
-  if (has2) m = fmaxf(m, t[2]);
-  m = grp_max(m);
+// log-sum-exp over the ten components of one pixel (own slots, fixed tree;
+// -infinity in a slot without a component)
+NXD float lse10(const float (&t)[3]) {
+  float m = xmax(t[0], t[1]);
+  m = grp_max(xmax(m, t[2]));
   float s = xexp(t[0] - m) + xexp(t[1] - m);
-  s = s + (has2 ? xexp(t[2] - m) : 0.0f);
+  s = s + xexp(t[2] - m);
   s = grp_sum(s);
   return m + xlog(s);
 }
@@ -704,14 +712,14 @@ NXD void mix_prep(const f4 (&rows)[HEAD_TILES], Mix& M, bool has2) {
 #pragma unroll
   for (int j = 0; j < 3; ++j) lam[j] = head_slot(hd, 10 * j);
   if (!has2) lam[2] = -INFINITY;
-  const float lse = lse10(lam, has2);
+  const float lse = lse10(lam);
 #pragma unroll
   for (int j = 0; j < 3; ++j) {
     M.logw[j] = lam[j] - lse;
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
       M.mu[c][j] = head_slot(hd, 10 * j + 1 + c);
-      M.invs[c][j] = xexp(-fmaxf(head_slot(hd, 10 * j + 4 + c), -7.0f));
+      M.invs[c][j] = xexp(-xmax(head_slot(hd, 10 * j + 4 + c), -7.0f));
       M.co[c][j] = xtanh(head_slot(hd, 10 * j + 7 + c));
     }
   }
@@ -793,7 +801,7 @@ NXD float posterior(Mix& M, int x, const float (&mu)[3], const float (&is)[3], b
 #pragma unroll
   for (int j = 0; j < 3; ++j) t[j] = M.logw[j] + log_bin(x, mu[j], is[j]);
   if (!has2) t[2] = -INFINITY;
-  const float lse = lse10(t, has2);
+  const float lse = lse10(t);
 #pragma unroll
   for (int j = 0; j < 3; ++j) M.logw[j] = t[j] - lse;
   return lse;
@@ -848,7 +856,7 @@ NXD void mix_prep16(const float* hp, int m, Mix16& M) {
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
     M.mu[c] = hp[head_row(mm, 1 + c)];
-    M.invs[c] = xexp(-fmaxf(hp[head_row(mm, 4 + c)], -7.0f));
+    M.invs[c] = xexp(-xmax(hp[head_row(mm, 4 + c)], -7.0f));
     M.co[c] = xtanh(hp[head_row(mm, 7 + c)]);
   }
 }

@@ -70,7 +70,7 @@ NXD float mix_joint(const f4 (&rows)[HEAD_TILES], const int (&xv)[3], bool has2,
 #pragma unroll
   for (int j = 0; j < 3; ++j) lam[j] = head_slot(hd, 10 * j);
   if (!has2) lam[2] = -INFINITY;
-  const float lse = lse10(lam, has2);
+  const float lse = lse10(lam);
   float L[3], gmu[3][3], gis[3][3], is[3][3], co[3][3], rho[3][3];
 #pragma unroll
   for (int j = 0; j < 3; ++j) {
@@ -84,13 +84,13 @@ NXD float mix_joint(const f4 (&rows)[HEAD_TILES], const int (&xv)[3], bool has2,
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
       rho[c][j] = head_slot(hd, 10 * j + 4 + c);
-      is[c][j] = xexp(-fmaxf(rho[c][j], -7.0f));
+      is[c][j] = xexp(-xmax(rho[c][j], -7.0f));
       lp[c] = log_bin_grad(xv[c], mu[c], is[c][j], gmu[c][j], gis[c][j]);
     }
     L[j] = (lam[j] - lse) + ((lp[0] + lp[1]) + lp[2]);
   }
   if (!has2) L[2] = -INFINITY;
-  const float logp = lse10(L, has2);
+  const float logp = lse10(L);
   if (GRAD) {
     const float s2 = -scale * kLog2e;  // d(scale * bits)/d log p
     f4 dh[HEAD_SLOTS];
