@@ -38,7 +38,8 @@ DECODE_TRAFFIC = {
     "sheared": {"src_sha": "6ea9303953709ce0", "patch": (82, 64), "interleave": 16,
                 "fetch_kib": 39794.6, "write_kib": 780929.6, "fetch_scale": 1.99982, "write_scale": 1.0},
 }
-KERNEL_SOURCES = ("nx_kernels.hip", "nx_team.hip", "nx_coder.hpp", "nx_device.hpp", "nx_layout.hpp", "nx_kernels.hpp", "nx_order.hpp")
+KERNEL_SOURCES = ("nx_kernels.hip", "nx_team.hip", "nx_coder.hpp", "nx_device.hpp", "nx_layout.hpp", "nx_kernels.hpp", "nx_order.hpp",
+                  "nx_window.hpp")
 
 
 def kernel_sources_sha() -> str:

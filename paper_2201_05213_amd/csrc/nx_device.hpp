@@ -21,6 +21,7 @@
 #include <stdint.h>
 
 #include "nx_layout.hpp"
+#include "nx_window.hpp"
 
 namespace nx {
 
@@ -602,11 +603,6 @@ NXD void net_quad(const float* __restrict__ w, int nb, const float (&cx)[NQ][qua
 // Contexts for net_quad of a pixel per lane 4 a + r: each lane loads its
 // inputs k = 16 j + a, clamped into the lane's pixels and masked as
 // gather_clamped does, or from the sheared window as gather_ring does.
-template <int H_>
-NXD void quad_tap(int j, int lane, int& k, int& dy) {
-  k = min(16 * j + (lane >> 2), 4 * conv_chunks(H_) - 1);
-  dy = min(k / (3 * (2 * H_ + 1)), H_);
-}
 template <int H_>
 NXD void quad_gather_image(float (&cx)[quad_inputs(H_)], const uint8_t* img, int W, int y0, int x0, int Hl, int Wl, int i,
                            int j, int lane) {

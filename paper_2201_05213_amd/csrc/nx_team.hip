@@ -18,35 +18,24 @@
 #include <algorithm>
 
 #include "nx_coder.hpp"
+#include "nx_window.hpp"
 
 namespace nx {
 
 // ------------------------------------------------------------------ context window in LDS
-// The sheared window of nx_layout.hpp in LDS: the last 16 wavefront steps
-// (columns) of the team's rows, int16 numerators 2x - 255, 0 off the lane,
-// planes [column][channel][row] with H_ rows on top. Input k of a pixel at
-// step t (window row dy) is plane 3 (t - H_(H_+2)) + k - 3 H_ dy (mod 48),
-// row i + dy; every column is held twice, 48 planes apart, so a step's planes
-// follow each other without a wrap.
-constexpr int WIN_PLANES = 2 * 3 * RING_COLS;
-
-// Pixel r = lane % 4 of a wave's four, block a = lane / 4: value j of the lane
-// is input k = 16 j + a of the pixel. What its place in the window has besides
-// the step and the pixel's row is the lane's for good.
+// (its places: nx_window.hpp)
+// What an input's place has besides the step and the pixel's row is the
+// lane's for good.
 template <int H_>
 NXD void quad_offsets(int (&off)[quad_inputs(H_)], int rows, int lane) {
 #pragma unroll
-  for (int j = 0; j < quad_inputs(H_); ++j) {
-    const int k = min(16 * j + (lane >> 2), 4 * conv_chunks(H_) - 1);
-    const int dy = min(k / (3 * (2 * H_ + 1)), H_);
-    off[j] = (k - 3 * H_ * dy) * rows + dy;
-  }
+  for (int j = 0; j < quad_inputs(H_); ++j) off[j] = win_tap<H_>(rows, j, lane);
 }
 // contexts of the wave's pixels at step t, i the window row of the lane's
 template <int H_>
 NXD void quad_gather(float (&cx)[quad_inputs(H_)], const int (&off)[quad_inputs(H_)], const int16_t* win, int rows,
                      int t, int i) {
-  const int16_t* b = win + 3 * ((t - H_ * (H_ + 2)) & (RING_COLS - 1)) * rows + i;
+  const int16_t* b = win + win_origin<H_>(rows, t, i);
   int raw[quad_inputs(H_)];
 #pragma unroll
   for (int j = 0; j < quad_inputs(H_); ++j) raw[j] = b[off[j]];
@@ -56,12 +45,23 @@ NXD void quad_gather(float (&cx)[quad_inputs(H_)], const int (&off)[quad_inputs(
 
 // both copies of plane `plane` (of column t), row r
 NXD void win_put(int16_t* win, int rows, int t, int ch, int r, int v) {
-  int16_t* b = win + (3 * (t & (RING_COLS - 1)) + ch) * rows + r;
+  int16_t* b = win + win_place(rows, t, ch, r);
   b[0] = (int16_t)v;
-  b[3 * RING_COLS * rows] = (int16_t)v;
+  b[win_copy(rows)] = (int16_t)v;
 }
 
 constexpr int TEAM_WAVES = ROW_WAVES;
+
+// A barrier at the head of a loop whose end writes the window. The wait for a
+// wave's LDS operations that __syncthreads() holds is not enough there: ROCm
+// 7.2's compiler drops it where nothing is in flight on the way into the loop,
+// and then the writes that come round the loop may still be in flight behind
+// the barrier. This wait (lgkmcnt(0) alone) is an instruction of its own, which
+// it keeps.
+NXD void team_barrier() {
+  __builtin_amdgcn_s_waitcnt(0xc07f);
+  __syncthreads();
+}
 
 // ------------------------------------------------------------------ mixture, 16 lanes per pixel
 template <int M>
@@ -213,12 +213,11 @@ __global__ void __launch_bounds__(2 * TEAM_WAVES * 64) k_decode_team(DecArgs A) 
   int32_t* sh = (int32_t*)(base + tw - TEAM_SH_WORDS);
   constexpr int o = H_ + 1;
   const bool live = m < 10;
-  // the pixels (rows of the group) of a wave: four in a row, so that a group of
-  // few rows leaves whole waves free, and with two teams on other SIMDs (wave
-  // w is on SIMD w mod 4); with K = 8, rows r and r + 8 share a stream and a wave
+  // the rows of the group of a wave's pixels (team_row), with two teams on
+  // other SIMDs (wave w is on SIMD w mod 4)
   const int v4 = (w4 + 2 * team) & (TEAM_WAVES - 1);
-  auto slot_of = [&](int q) { return KIND == POPS_ROWS && K == 8 ? 2 * v4 + (q & 1) + 8 * (q >> 1) : 4 * v4 + q; };
-  const int slot = slot_of(s), nslot = slot_of(lane & 3);  // the mixture's pixel, the network's
+  const bool pairs = KIND == POPS_ROWS && K == 8;
+  const int slot = team_row(v4, s, pairs), nslot = team_row(v4, lane & 3, pairs);  // the mixture's pixel, the network's
   int off[quad_inputs(H_)];
   quad_offsets<H_>(off, rows, lane);
   // barriers of one group
@@ -227,7 +226,8 @@ __global__ void __launch_bounds__(2 * TEAM_WAVES * 64) k_decode_team(DecArgs A) 
   // the team's lane
   int left = 0;        // groups left
   bool done = false;   // no lanes left for this team
-  int n = 0, y0 = 0, x0 = 0, Hl = 0, Wl = 0, W = 0, gi = 0, ts = 0, ihi = -1;
+  int n = 0, y0 = 0, x0 = 0, Hl = 0, Wl = 0, W = 0;
+  TeamGroup G = TEAM_START;
   uint8_t* img = nullptr;
   uint64_t seed = 0;
   uint32_t* dump = nullptr;
@@ -313,18 +313,12 @@ __global__ void __launch_bounds__(2 * TEAM_WAVES * 64) k_decode_team(DecArgs A) 
         if (!ok && lane == 0) sh[1] = 0;
         // the lane's groups of 16 rows
         const int T = Wl + o * (Hl - 1);
-        for (int t = lane; t < T; t += 64) {
-          int a, b;
-          step_rows(t, Hl, Wl, o, a, b);
-          total += a <= b ? (b - a) / 16 + 1 : 0;
-        }
+        for (int t = lane; t < T; t += 64) total += team_groups_at(t, Hl, Wl, o);
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) total += __shfl_xor(total, d, 64);
         total = uniform(total);
         for (int k = w4 * 64 + lane; k < WIN_PLANES * rows / 2; k += TEAM_WAVES * 64) ((uint32_t*)win)[k] = 0u;
-        gi = -1;  // the first group is found by the step loop
-        ts = 0;
-        ihi = -1;
+        G = TEAM_START;
       }
     }
     __syncthreads();
@@ -351,26 +345,17 @@ __global__ void __launch_bounds__(2 * TEAM_WAVES * 64) k_decode_team(DecArgs A) 
         for (int b = 0; b < n_bar; ++b) __syncthreads();
         continue;
       }
-      // the next group: 16 rows from ts on of step gi
-      ts += 16;
-      if (ts > ihi) {
-        do {
-          ++gi;
-          step_rows(gi, Hl, Wl, o, ts, ihi);
-          // the window's column gi: the step's rows are written as they
-          // decode; of the others those that a later read can reach are
-          // cleared (see decode_lane)
-          const int r = ts <= ihi ? (lane < H_ ? ts - H_ + lane : ihi + 1 + (lane - H_)) : ts - H_ + lane;
-          const int nz = ts <= ihi ? 2 * H_ + 1 : 2 * H_ + 1 + (ihi + 1 - ts);
-          if (w4 == TEAM_WAVES - 1 && lane < nz && r >= 0 && r < Hl) {
+      team_next<H_>(
+          G, Hl, Wl, [] { team_barrier(); },
+          [&] {
+            const int r = w4 == TEAM_WAVES - 1 ? team_clear_row<H_>(G, Hl, lane) : -1;
+            if (r >= 0) {
 #pragma unroll
-            for (int c = 0; c < 3; ++c) win_put(win, rows, gi, c, H_ + r, 0);
-          }
-        } while (ts > ihi);
-      }
+              for (int c = 0; c < 3; ++c) win_put(win, rows, G.step, c, H_ + r, 0);
+            }
+          });
       --left;
-      const int na = uniform(min(16, ihi - ts + 1));
-      __syncthreads();  // the window as the last group left it
+      const int gi = uniform(G.step), ts = uniform(G.ts), na = uniform(min(16, G.last - G.ts + 1));
       const int i = ts + slot, j = gi - o * i;
       const bool act = slot < na;
       // a wave without a pixel has nothing to do, or (serial pops) the barriers and its pops
