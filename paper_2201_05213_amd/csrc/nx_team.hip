@@ -642,7 +642,7 @@ __device__ void decode_band(const DecArgs& A, const float* w, float* hbs, int16_
     int off[quad_inputs(H_)];
     quad_offsets<H_>(off, rows, lane);
     for (int t = t_lo; t <= t_hi; ++t) {
-      __syncthreads();
+      team_barrier();
       const int j = t - o * i;
       const bool act = i <= r1 && j >= 0 && j < Wl;
       int xv[3] = {0, 0, 0};
