@@ -1387,17 +1387,13 @@ static hipError_t pass_t(const PassArgs& a, int grid, hipStream_t s) {
 }
 
 // A wave's LDS: pivot and mixture tables, or a head table of as many pixels
-// (a multiple of 4, at most 12) as the LDS left by the weights gives each
-// wave. Groups of at most that many pixels take net_quad, at 3,650 cycles of
-// matrix instructions per four pixels (model B) against 14,100 for a tile.
-// Measured with the sheared window's shorter gather, 4 1024 x 1024 and 2
-// 2048 x 1536 images in 82 x 64 patches (96 of a patch's 388 steps have at
-// most 12 rows): 8.71 -> 8.35 ms.
+// (a multiple of 4, at most quad_limit) as the LDS left by the weights gives
+// each wave. Groups of at most that many pixels take net_quad.
 template <int H_, int C_, int K, bool SAMPLE = false>
 static hipError_t decode_tt(const DecArgs& args, int grid, int waves, size_t lim, hipStream_t s) {
   DecArgs a = args;
   const int64_t left = ((int64_t)lim / 4 - a.wfloats) / waves;
-  a.quad_px = (int)std::min<int64_t>(12, left / HB_STRIDE / 4 * 4);
+  a.quad_px = (int)std::min<int64_t>(quad_limit(C_), left / HB_STRIDE / 4 * 4);
   a.wave_words = std::max(WAVE_LDS_WORDS, a.quad_px * HB_STRIDE);
   const size_t lds = ((size_t)a.wfloats + (size_t)waves * a.wave_words) * 4;
   if (a.order == 2)

@@ -77,6 +77,16 @@ struct PackArgs {
   int64_t max_stream_bytes;  // an estimate of the longest stream, for the grid
 };
 
+// The largest group of pixels that the wave-per-lane decoder takes by fours
+// (net_quad); larger ones take a tile of 16 (net_forward). A tile's matrix
+// instructions do the work of 16 outputs and 16 pixels in 32 cycles, a quad's of
+// 64 outputs, used or not, and four pixels in 8: what a quad costs against a tile
+// goes as 1 / C. Time of groups of 4, 8 and 12 pixels by quads against tiles
+// (768 to 2,048 lanes, either layout, 1 to 3 blocks): 64 channels 1.48-1.80, 1.31-1.50 and
+// 1.10-1.21 times as fast; 32 channels 1.14-1.29, 1.02-1.10 and 0.89-0.97; 16
+// channels 1.00-1.08, 0.88-0.99 and 0.74-0.89.
+constexpr int quad_limit(int C) { return C >= 64 ? 12 : C >= 32 ? 8 : 4; }
+
 struct DecArgs {
   const float* w;
   int64_t wfloats;
