@@ -226,7 +226,11 @@ __global__ void __launch_bounds__(64) k_rans_counts(RansEncArgs A) {
   if (lane == 0) A.lane_len[SL] = (uint32_t)min<int64_t>(suf, G.rev_cap);
 }
 
-// What coding a symbol (s, f) needs besides the state: y / f is the high
+// What coding a symbol (s, f) needs besides the state (a table entry per symbol
+// with a reciprocal for the division, a bias that makes good the reciprocal of
+// f = 1, and the factor 2^16 - f: the method of F. Giesen's public-domain rANS coder
+// (rans_byte.h), whose exact reciprocals are those of R. Alverson, "Integer
+// division using reciprocals", 1991): y / f is the high
 // word of y M, shifted right by sh, exactly, for every y < 2^31 (M =
 // ceil(2^(32 + sh) / f), 2^sh < f <= 2^(sh + 1), so M f exceeds the power of
 // two by e < f <= 2^(sh + 1) and y e < 2^(32 + sh)). For f = 1, M would be
@@ -316,8 +320,7 @@ NXD uint32_t put_state(uint32_t x, const PutSym& e) {
 // The bytes a thread sheds over PUT_BATCH symbols gather in its window in LDS,
 // downwards from the window's end, and go to memory as whole words: a store
 // of each symbol's bytes is a transaction of its own at the L2, which bounded
-// the coder of the large batch (30,720 streams of 1,024 symbols on average: 195 us with
-// a store a symbol, 152 us so).
+// the coder of a large batch.
 constexpr int PUT_BATCH = 16;
 constexpr int PUT_WINDOW = 2 * PUT_BATCH;  // two bytes a symbol at most
 constexpr int PUT_STRIDE = PUT_WINDOW + 16;
@@ -483,8 +486,9 @@ __global__ void __launch_bounds__(64) k_rans_enc_wave(RansEncArgs A) {
 // One thread per stream (lane L, stream k: index L K + k), PUT_BATCH symbols
 // at a time, the next in flight: a wave waits for a line of 32 symbols from
 // HBM once in two rounds, and a round is longer than that takes. Bound by
-// the 29 instructions of a symbol on a wave alone on its SIMD: 132 us for the
-// large batch (it took 224 us with a branch and up to two byte stores each).
+// the 29 instructions of a symbol on a wave alone on its SIMD: 133 us for
+// 32,512 streams of 968 symbols on average (226 us with a branch and up to two
+// byte stores a symbol).
 __global__ void __launch_bounds__(64) k_rans_enc(RansEncArgs A) {
   __shared__ __align__(16) uint8_t shed[64 * PUT_STRIDE];
   const int64_t SL = (int64_t)blockIdx.x * 64 + threadIdx.x;
@@ -578,9 +582,8 @@ NXD uint64_t wave_scan(uint64_t v, int lane) {
 
 // per image: lane_end (inclusive prefix of lane lengths), container bytes.
 // SCAN_THREADS streams a round: sums within each wave by lane shuffles, then
-// over the waves through LDS (two barriers a round; the large
-// batch's 30,720 streams took 43 us with 256 threads and a barrier a doubling,
-// under 10 us so)
+// over the waves through LDS (two barriers a round; 32,512 streams of 6 images
+// took 43 us with 256 threads and a barrier a doubling, 12 us so)
 constexpr int SCAN_THREADS = 1024;
 __global__ void __launch_bounds__(SCAN_THREADS) k_lane_scan(PackArgs A) {
   __shared__ uint32_t part[SCAN_THREADS / 64];
@@ -1403,9 +1406,9 @@ static hipError_t decode_tt(const DecArgs& args, int grid, int waves, size_t lim
   return hipGetLastError();
 }
 
-// the decoder's dynamic LDS limit, raised to the device maximum once per
-// kernel before any launch (not a stream operation: kept out of the launch
-// path, which a caller may capture)
+// the decoder's dynamic LDS limit, raised to the device maximum by every
+// prepare call (not a stream operation: kept out of the launch path, which a
+// caller may capture)
 template <int H_, int C_, int K>
 static hipError_t decode_setup_k() {
   int dev = 0, lim = 0;
@@ -1510,8 +1513,8 @@ hipError_t launch_pack(const PackArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(k_lane_scan, dim3(a.n_img), dim3(SCAN_THREADS), 0, s, a);
   hipLaunchKernelGGL(k_img_scan, dim3(1), dim3(64), 0, s, a);
   if (a.n_streams > 0) {
-    // a stream's bytes are at most two per symbol; a lane's symbols spread
-    // over its K streams (row streams: a row of them)
+    // parts of a stream of the estimated length; a longer one (up to two bytes
+    // a symbol) has its blocks take more than one part each
     const int64_t parts = (a.max_stream_bytes + PACK_PART - 1) / PACK_PART;
     hipLaunchKernelGGL(k_pack, dim3((unsigned)a.n_streams, (unsigned)std::max<int64_t>(1, std::min<int64_t>(parts, 64))),
                        dim3(64), 0, s, a);

@@ -181,17 +181,26 @@ hipError_t launch_decode_rows(int h, int C, const DecArgs& a, int grid, hipStrea
 // Few lanes: teams of four waves per lane (nx_team.hip), `teams` lanes a
 // workgroup and CU. decode_teams: how many, or 0 for the wave-per-lane
 // decoder (launch_decode, launch_sample). A lone wave issues a group of 16
-// pixels in 26 to 32 thousand cycles (model B), a team in 14 to 17; two teams
-// share their SIMDs' issue (20 thousand for a group of each, 512 thumbnails) and still
-// beat two lone waves (36); three or four would not. So the line is at two lanes per
-// CU, in either wavefront layout, where `rows` (window rows of the tallest
-// lane) fit the LDS left by the weights.
+// pixels in 26 to 32 thousand cycles (h = 3, 64 channels, 2 blocks), a team in
+// 14 to 17; two teams share their SIMDs' issue, 20 thousand for a group of
+// each. Measured, a wave per lane against teams, nine model sizes, lanes from
+// 20 x 20 to 64 x 64, 12 x 100 and 90 x 8, every kind of pops:
+//   one lane per CU   one team 1.13 to 1.93 times as fast (256 lanes of 64 x 64,
+//                     8 streams, that model: 4.30 -> 2.23 ms)
+//   two               two teams 1.0 to 1.6 times (512 such lanes: 4.34 -> 3.34 ms),
+//                     but 0.95 to 1.06 with 8 streams and at most 10 rows a step,
+//                     where a wave has half of its four pixels (32 x 32: 1.41 ->
+//                     1.46 ms), and 0.94 to 1.10 with h = 1 and 16 channels
+//   three, four       0.50 to 0.86 (1,024 lanes of 32 x 32, 4 streams:
+//                     1.63 -> 2.65 ms)
+// So the line is at two lanes per CU, in either wavefront layout, where `rows`
+// (window rows of the tallest lane) fit the LDS left by the weights.
 // K: rANS streams per lane, 0 to sample (also DecArgs.K of the launch).
 int decode_teams(int K, int64_t wfloats, int64_t n_lanes, int order, int64_t rows, int cus, size_t lds);
 hipError_t launch_decode_team(int h, int C, const DecArgs& a, int teams, hipStream_t s);
 // raise the LDS limit of the team kernels, or of the row-stream decoder's
 hipError_t prepare_team(int h, int C, bool rows);
-// raise the decoder kernels' LDS limit (once, outside any stream capture)
+// raise the decoder kernels' LDS limit (at every prepare, outside any stream capture)
 hipError_t prepare_decode(int h, int C, int K);
 // waves per workgroup in 1..DECODE_WAVES (the LDS, of at most `lds` bytes, takes each wave's tables);
 // prepare_decode must have run for (h, C, a.K)
