@@ -504,17 +504,24 @@ NXD int find_img_band(const ImgDesc* __restrict__ d, int n, int64_t key) {
   return uniform(lo);
 }
 
-NXD void band_publish(int32_t* slot, int32_t v) {
-  __hip_atomic_store(slot, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+// the whole wave releases its stores, then its first lane publishes
+NXD void band_publish(int32_t* slot, int32_t v, int lane) {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+  __builtin_amdgcn_wave_barrier();
+  if (lane == 0) __hip_atomic_store(slot, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 template <int H_>
 constexpr int band_rows() { return (ROW_BAND + H_ + 3) / 4 * 4; }
 
 // The workgroup has a fifth wave, the band's link to its neighbours: after
-// each step's barrier it publishes the step and fetches the rows above for the
-// next, so that neither the release nor those loads are on the team's path
-// (1,100 of 16,500 cycles a step when the team's first wave did it).
+// each step's barrier it stores the step's pixels, publishes the step and
+// fetches the rows above for the next, so that neither the release nor those
+// loads are on the team's path (1,100 of 16,500 cycles a step when the team's
+// first wave did it). The pixels are its stores because a release waits for
+// the stores of its own wave alone, and a barrier of the workgroup for no
+// store to memory: another wave's could still be on their way when the step
+// is published.
 constexpr int ROW_BLOCK = 64 * (ROW_WAVES + 1);
 
 template <int H_, int C_>
@@ -588,7 +595,7 @@ __device__ void decode_band(const DecArgs& A, const float* w, float* hbs, int16_
   if (mismatch || !ok) {
     if (threadIdx.x == 0) {
       A.status[n] = mismatch ? ST_MISMATCH : ST_CORRUPT;
-      band_publish(mine, BAND_DONE);  // the band below must not wait for this one
+      band_publish(mine, BAND_DONE, 0);  // the band below must not wait for this one
     }
     __syncthreads();
     return;
@@ -602,6 +609,14 @@ __device__ void decode_band(const DecArgs& A, const float* w, float* hbs, int16_
     const int uq = min(lane / 3, H_ - 1), uc = lane - 3 * (lane / 3);
     const int i = r0 - 1 - uq;
     const gbytes row = as_global(img + ((int64_t)(y0 + max(i, 0)) * D.W + x0) * 3 + uc);
+    // the band's pixels of step t, from the window: lane 3 q + c channel c of row r0 + q
+    const int sq = min(lane / 3, ROW_BAND - 1), sc = lane - 3 * (lane / 3);
+    auto store = [&](int t) {
+      const int is = r0 + sq, j = t - o * is;
+      const int v = win[win_place(rows, t, sc, H_ + sq)];
+      if (lane < 3 * ROW_BAND && is <= r1 && j >= 0 && j < Wl)
+        D.px[((int64_t)(y0 + is) * D.W + (x0 + j)) * 3 + sc] = (uint8_t)((v + 255) >> 1);
+    };
     auto fetch = [&](int t) {
       const int j = t - o * i;
       const bool in = bb > 0 && i >= 0 && j >= 0 && j < Wl;
@@ -630,12 +645,15 @@ __device__ void decode_band(const DecArgs& A, const float* w, float* hbs, int16_
       if (t == t_lo)  // the window's columns before the band's first step
         for (int d = H_ * (H_ + 2); d > 1; --d) fetch(t - d);
       fetch(t - 1);
-      // the band's step t - 1 is finished in every wave (its pixels stored)
+      // the band's step t - 1 is finished in every wave (its pixels in the window)
       __syncthreads();
-      if (lane == 0) band_publish(mine, t);
+      if (t > t_lo) store(t - 1);
+      band_publish(mine, t, lane);
     }
+    __syncthreads();
+    store(t_hi);
+    band_publish(mine, BAND_DONE, lane);
   } else {
-    uint8_t* img = D.px + ((int64_t)(y0 + r0 + pp) * D.W + x0) * 3 + m;  // this lane's row (used where it is one)
     uint32_t* dump = A.sym_dump ? A.sym_dump + D.px_base * 3 : nullptr;
     const bool live = m < 10;
     const int i = r0 + pp;
@@ -679,13 +697,11 @@ __device__ void decode_band(const DecArgs& A, const float* w, float* hbs, int16_
       // the window's column t: the decoded pixels, 0 in the other rows
       if (m < 3) {
         const int v = m == 0 ? xv[0] : (m == 1 ? xv[1] : xv[2]);
-        if (act) img[3 * j] = (uint8_t)v;
         win_put(win, rows, t, m, H_ + pp, act ? 2 * v - 255 : 0);
       }
     }
+    team_barrier();
   }
-  __syncthreads();
-  if (threadIdx.x == 0) band_publish(mine, BAND_DONE);
   // every row's stream must end in the start state with every byte read
   if (!link && pp < nrows && m == 0 && !(P.x == RANS_X0 && P.pos == P.len)) A.status[n] = ST_CORRUPT;
   __syncthreads();
