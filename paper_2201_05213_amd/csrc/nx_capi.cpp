@@ -611,6 +611,11 @@ nellox_status nellox_peek(const uint8_t* c, size_t len, int32_t* H, int32_t* W, 
   return NELLOX_OK;
 }
 
+// lanes per CU decoded by teams of waves, 0: a wave per lane
+static int teams_of(const nellox_model* m, int K, int64_t n_lanes, int order, int64_t rows) {
+  return decode_teams(K, m->wfloats, n_lanes, order, rows, m->num_cu, m->lds);
+}
+
 static nellox_status prepare_impl(nellox_model* m, int32_t n, const nellox_image* outs, const nellox_opts* o,
                                   void* ws, size_t ws_bytes, nellox_decode_plan* plan, void* stream) {
   if (check_model(m)) return NELLOX_E_ARG;
@@ -651,15 +656,12 @@ static nellox_status prepare_impl(nellox_model* m, int32_t n, const nellox_image
   plan->ws_bytes = W.small;
   plan->desc_offset = W.desc;
   plan->counter_offset = W.flags + 4;
-  hipError_t e = P.K == ROW_STREAMS ? hipSuccess : prepare_decode(m->h, m->Cp, P.K);
-  if (e == hipSuccess) e = prepare_team(m->h, m->Cp, P.K == ROW_STREAMS);
+  // the decoder that run_impl takes for this plan, and no other: it runs on every call
+  const hipError_t e = P.K == ROW_STREAMS ? prepare_rows(m->h, m->Cp)
+                       : teams_of(m, P.K, P.n_lanes, P.order, plan->ring_rows) ? prepare_team(m->h, m->Cp, P.K)
+                                                                               : prepare_decode(m->h, m->Cp, P.K);
   if (e != hipSuccess) return hip_fail(e, "decoder set-up");
   return NELLOX_OK;
-}
-
-// lanes per CU decoded by teams of waves, 0: a wave per lane
-static int teams_of(const nellox_model* m, int K, int64_t n_lanes, int order, int64_t rows) {
-  return decode_teams(K, m->wfloats, n_lanes, order, rows, m->num_cu, m->lds);
 }
 
 static nellox_status run_impl(nellox_model* m, const nellox_decode_plan* plan, const uint8_t* in,
@@ -798,7 +800,7 @@ nellox_status nellox_sample(const nellox_model* mc, int32_t n, const uint64_t* s
   uint8_t* w8 = (uint8_t*)ws;
   const int64_t rows = ring_rows_for(P.ph_max, m->h);
   const int teams = teams_of(m, 0, P.n_lanes, o->order, rows);
-  hipError_t e = teams ? prepare_team(m->h, m->Cp, false) : prepare_decode(m->h, m->Cp, 4);
+  hipError_t e = teams ? prepare_team(m->h, m->Cp, 0) : prepare_decode(m->h, m->Cp, 4);
   if (e != hipSuccess) return hip_fail(e, "sampler set-up");
   if ((st = upload_plan(m, P, w8, W, s))) return st;
   int32_t* counter = (int32_t*)(w8 + W.flags + 4);

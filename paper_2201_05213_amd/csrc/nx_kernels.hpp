@@ -198,8 +198,9 @@ hipError_t launch_decode_rows(int h, int C, const DecArgs& a, int grid, hipStrea
 // K: rANS streams per lane, 0 to sample (also DecArgs.K of the launch).
 int decode_teams(int K, int64_t wfloats, int64_t n_lanes, int order, int64_t rows, int cus, size_t lds);
 hipError_t launch_decode_team(int h, int C, const DecArgs& a, int teams, hipStream_t s);
-// raise the LDS limit of the team kernels, or of the row-stream decoder's
-hipError_t prepare_team(int h, int C, bool rows);
+// raise the LDS limit of the team kernel for K, or of the row-stream decoder
+hipError_t prepare_team(int h, int C, int K);
+hipError_t prepare_rows(int h, int C);
 // raise the decoder kernels' LDS limit (at every prepare, outside any stream capture)
 hipError_t prepare_decode(int h, int C, int K);
 // waves per workgroup in 1..DECODE_WAVES (the LDS, of at most `lds` bytes, takes each wave's tables);

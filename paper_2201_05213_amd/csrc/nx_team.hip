@@ -193,6 +193,7 @@ NXHD int64_t team_words(int64_t rows, bool serial) {
 // queue the workgroup runs as many groups as the team nearest its lane's end
 // has left, and a team without a lane runs the barriers alone.
 constexpr int POPS_ROWS = 0, POPS_SERIAL = 1, POPS_SAMPLE = 2;
+static int pops_kind(int K) { return K == 0 ? POPS_SAMPLE : K >= 8 ? POPS_ROWS : POPS_SERIAL; }
 
 template <int H_, int C_, int KIND>
 __global__ void __launch_bounds__(2 * TEAM_WAVES * 64) k_decode_team(DecArgs A) {
@@ -744,20 +745,26 @@ static hipError_t lds_limit(int& lim) {
 }
 
 template <int H_, int C_>
-static hipError_t team_setup_t(bool rows) {
+static hipError_t team_setup_t(int K) {
   int lim = 0;
-  hipError_t e = lds_limit(lim);
-  if (rows) {
-    if (e == hipSuccess) e = allow_lds(k_decode_rows<H_, C_>, (size_t)lim);
-    return e;
-  }
-  if (e == hipSuccess) e = allow_lds(k_decode_team<H_, C_, POPS_ROWS>, (size_t)lim);
-  if (e == hipSuccess) e = allow_lds(k_decode_team<H_, C_, POPS_SERIAL>, (size_t)lim);
-  if (e == hipSuccess) e = allow_lds(k_decode_team<H_, C_, POPS_SAMPLE>, (size_t)lim);
-  return e;
+  const hipError_t e = lds_limit(lim);
+  if (e != hipSuccess) return e;
+  const int kind = pops_kind(K);
+  if (kind == POPS_ROWS) return allow_lds(k_decode_team<H_, C_, POPS_ROWS>, (size_t)lim);
+  if (kind == POPS_SERIAL) return allow_lds(k_decode_team<H_, C_, POPS_SERIAL>, (size_t)lim);
+  return allow_lds(k_decode_team<H_, C_, POPS_SAMPLE>, (size_t)lim);
 }
 
-hipError_t prepare_team(int h, int C, bool rows) { NX_DISPATCH(team_setup_t, h, C, rows); }
+template <int H_, int C_>
+static hipError_t rows_setup_t() {
+  int lim = 0;
+  const hipError_t e = lds_limit(lim);
+  return e == hipSuccess ? allow_lds(k_decode_rows<H_, C_>, (size_t)lim) : e;
+}
+
+hipError_t prepare_team(int h, int C, int K) { NX_DISPATCH(team_setup_t, h, C, K); }
+
+hipError_t prepare_rows(int h, int C) { NX_DISPATCH(rows_setup_t, h, C); }
 
 static size_t team_lds(int64_t wfloats, int teams, int rows, bool serial) {
   return (size_t)(wfloats + teams * team_words(rows, serial)) * sizeof(float);
@@ -785,8 +792,7 @@ static hipError_t team_t(const DecArgs& a, int kind, int teams, hipStream_t s) {
 hipError_t launch_decode_team(int h, int C, const DecArgs& a, int teams, hipStream_t s) {
   if (a.n_lanes == 0) return hipSuccess;
   if (teams < 1 || teams > 2 || (a.K != 0 && !valid_interleave(a.K))) return hipErrorInvalidValue;
-  const int kind = a.K == 0 ? POPS_SAMPLE : a.K >= 8 ? POPS_ROWS : POPS_SERIAL;
-  NX_DISPATCH(team_t, h, C, a, kind, teams, s);
+  NX_DISPATCH(team_t, h, C, a, pops_kind(a.K), teams, s);
 }
 
 template <int H_, int C_>
