@@ -1396,7 +1396,7 @@ template <int H_, int C_, int K, bool SAMPLE = false>
 static hipError_t decode_tt(const DecArgs& args, int grid, int waves, size_t lim, hipStream_t s) {
   DecArgs a = args;
   const int64_t left = ((int64_t)lim / 4 - a.wfloats) / waves;
-  a.quad_px = (int)std::min<int64_t>(quad_limit(C_), left / HB_STRIDE / 4 * 4);
+  a.quad_px = (int)std::min<int64_t>(quad_limit(C_, a.nb), left / HB_STRIDE / 4 * 4);
   a.wave_words = std::max(WAVE_LDS_WORDS, a.quad_px * HB_STRIDE);
   const size_t lds = ((size_t)a.wfloats + (size_t)waves * a.wave_words) * 4;
   if (a.order == 2)

@@ -84,8 +84,12 @@ struct PackArgs {
 // goes as 1 / C. Time of groups of 4, 8 and 12 pixels by quads against tiles
 // (768 to 2,048 lanes, either layout, 1 to 3 blocks): 64 channels 1.48-1.80, 1.31-1.50 and
 // 1.10-1.21 times as fast; 32 channels 1.14-1.29, 1.02-1.10 and 0.89-0.97; 16
-// channels 1.00-1.08, 0.88-0.99 and 0.74-0.89.
-constexpr int quad_limit(int C) { return C >= 64 ? 12 : C >= 32 ? 8 : 4; }
+// channels 1.00-1.08, 0.88-0.99 and 0.74-0.89. With 16 channels a block's two
+// layers are longer by fours, chains of 16 dependent instructions with a
+// transpose each, so that what the gather saves is used up after about four
+// blocks (raster order, h = 3, 0 to 24 blocks: 1.03, 1.02, 1.01, 1.00 with 3,
+// 0.995 with 4, 0.98 with 6, 0.97 with 8, 0.92 with 24; 32 channels 1.2 with 8).
+constexpr int quad_limit(int C, int nb = 0) { return C >= 64 ? 12 : C >= 32 ? 8 : nb <= 4 ? 4 : 0; }
 
 struct DecArgs {
   const float* w;
