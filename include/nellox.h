@@ -73,9 +73,9 @@ typedef struct {
                          sheared layout (ShearLoC, Sec. 3.1, Algorithm 2): the coded order
                          and the containers of 2 are those of 1; a decoder with order 2
                          gathers each pixel's context from a window of the lane's
-                         sheared canvas, where every step is one column (with at
-                         most two lanes per CU orders 1 and 2 decode alike, from
-                         such a window in LDS) */
+                         sheared canvas, where every step is one column (a batch
+                         of few lanes, two per CU at most, is decoded alike with
+                         orders 1 and 2, from such a window in LDS) */
   int32_t patch_h;    /* patch rows; <= 0 or >= H: whole image */
   int32_t patch_w;    /* patch columns; <= 0 or >= W: whole image */
   int32_t interleave; /* rANS states per lane: 0 or 1 = one; 2, 4, 8 or 16 (wavefront
@@ -185,6 +185,7 @@ nellox_status nellox_decode_trace(const nellox_model* m, int32_t n, const uint8_
 typedef struct {
   int32_t n, order, interleave; /* images, decoding order, rANS streams per lane */
   int32_t grid, waves;          /* launch shape: workgroups, waves per workgroup */
+  int32_t step_rows;            /* the most rows of a wavefront step (0: not known) */
   int64_t n_lanes;              /* patches (lanes) of the batch */
   uint64_t model_hash;          /* the model the plan was made for */
   int64_t ws_bytes;             /* workspace bytes the plan occupies */

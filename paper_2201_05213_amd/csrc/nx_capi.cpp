@@ -612,8 +612,15 @@ nellox_status nellox_peek(const uint8_t* c, size_t len, int32_t* H, int32_t* W, 
 }
 
 // lanes per CU decoded by teams of waves, 0: a wave per lane
-static int teams_of(const nellox_model* m, int K, int64_t n_lanes, int order, int64_t rows) {
-  return decode_teams(K, m->wfloats, n_lanes, order, rows, m->num_cu, m->lds);
+static int teams_of(const nellox_model* m, int K, int64_t n_lanes, int order, int64_t rows, int step_rows) {
+  return decode_teams(TeamQuery{m->Cp, m->nb, K, order, m->wfloats, n_lanes, rows, step_rows, m->num_cu, m->lds});
+}
+
+// the most rows of a wavefront step of any lane
+static int most_step_rows(const Plan& P, int h) {
+  int r = 0;
+  for (const ImgDesc& D : P.d) r = std::max(r, std::min(D.ph, (D.pw + h) / (h + 1)));
+  return r;
 }
 
 static nellox_status prepare_impl(nellox_model* m, int32_t n, const nellox_image* outs, const nellox_opts* o,
@@ -651,6 +658,7 @@ static nellox_status prepare_impl(nellox_model* m, int32_t n, const nellox_image
   plan->grid = grid;
   plan->ring_offset = W.ring;
   plan->ring_rows = ring_rows_for(P.ph_max, m->h);
+  plan->step_rows = most_step_rows(P, m->h);
   plan->n_lanes = P.n_lanes;
   plan->model_hash = m->hash;
   plan->ws_bytes = W.small;
@@ -658,7 +666,7 @@ static nellox_status prepare_impl(nellox_model* m, int32_t n, const nellox_image
   plan->counter_offset = W.flags + 4;
   // the decoder that run_impl takes for this plan, and no other: it runs on every call
   const hipError_t e = P.K == ROW_STREAMS ? prepare_rows(m->h, m->Cp)
-                       : teams_of(m, P.K, P.n_lanes, P.order, plan->ring_rows) ? prepare_team(m->h, m->Cp, P.K)
+                       : teams_of(m, P.K, P.n_lanes, P.order, plan->ring_rows, plan->step_rows) ? prepare_team(m->h, m->Cp, P.K)
                                                                                : prepare_decode(m->h, m->Cp, P.K);
   if (e != hipSuccess) return hip_fail(e, "decoder set-up");
   return NELLOX_OK;
@@ -711,7 +719,8 @@ static nellox_status run_impl(nellox_model* m, const nellox_decode_plan* plan, c
   if (rows) {
     a.K = ROW_STREAMS;
     e = launch_decode_rows(m->h, m->Cp, a, plan->grid, s);
-  } else if (const int teams = teams_of(m, plan->interleave, plan->n_lanes, plan->order, plan->ring_rows)) {
+  } else if (const int teams = teams_of(m, plan->interleave, plan->n_lanes, plan->order, plan->ring_rows,
+                                        plan->step_rows)) {
     a.team_rows = (int)plan->ring_rows;
     e = launch_decode_team(m->h, m->Cp, a, teams, s);
   } else {
@@ -799,7 +808,7 @@ nellox_status nellox_sample(const nellox_model* mc, int32_t n, const uint64_t* s
   hipStream_t s = (hipStream_t)stream;
   uint8_t* w8 = (uint8_t*)ws;
   const int64_t rows = ring_rows_for(P.ph_max, m->h);
-  const int teams = teams_of(m, 0, P.n_lanes, o->order, rows);
+  const int teams = teams_of(m, 0, P.n_lanes, o->order, rows, most_step_rows(P, m->h));
   hipError_t e = teams ? prepare_team(m->h, m->Cp, 0) : prepare_decode(m->h, m->Cp, 4);
   if (e != hipSuccess) return hip_fail(e, "sampler set-up");
   if ((st = upload_plan(m, P, w8, W, s))) return st;

@@ -187,20 +187,48 @@ hipError_t launch_decode_rows(int h, int C, const DecArgs& a, int grid, hipStrea
 // decoder (launch_decode, launch_sample). A lone wave issues a group of 16
 // pixels in 26 to 32 thousand cycles (h = 3, 64 channels, 2 blocks), a team in
 // 14 to 17; two teams share their SIMDs' issue, 20 thousand for a group of
-// each. Measured, a wave per lane against teams, nine model sizes, lanes from
-// 20 x 20 to 64 x 64, 12 x 100 and 90 x 8, every kind of pops:
+// each. Measured, a wave per lane against teams, 37 model sizes, lanes from
+// 8 x 8 to 64 x 64, 12 x 100 and 90 x 8, every kind of pops:
 //   one lane per CU   one team 1.13 to 1.93 times as fast (256 lanes of 64 x 64,
-//                     8 streams, that model: 4.30 -> 2.23 ms)
-//   two               two teams 1.0 to 1.6 times (512 such lanes: 4.34 -> 3.34 ms),
-//                     but 0.95 to 1.06 with 8 streams and at most 10 rows a step,
-//                     where a wave has half of its four pixels (32 x 32: 1.41 ->
-//                     1.46 ms), and 0.94 to 1.10 with h = 1 and 16 channels
+//                     8 streams, that model: 4.30 -> 2.23 ms); with 16 channels
+//                     and 24 blocks 1.0 to 1.1, but 0.95 to 0.98 with 4 streams
+//   two               two teams 1.0 to 2.0 times (512 such lanes: 4.34 -> 3.34 ms)
+//                     where at most two of a team's waves have pixels, so that
+//                     the two teams are on different SIMDs, and with 2 streams.
+//                     Where more have, the network counts, which four pixels
+//                     take in a chain of single inputs: 64 channels 1.0 to 1.5
+//                     (0.95 with 8 streams), 32 channels 0.93 to 1.2 up to 3
+//                     blocks and 0.89 to 1.1 with 8, 16 channels 0.97 to 1.2
+//                     without blocks, 0.91 to 1.1 with 2, 0.79 to 1.0 with 8
 //   three, four       0.50 to 0.86 (1,024 lanes of 32 x 32, 4 streams:
 //                     1.63 -> 2.65 ms)
-// So the line is at two lanes per CU, in either wavefront layout, where `rows`
-// (window rows of the tallest lane) fit the LDS left by the weights.
-// K: rANS streams per lane, 0 to sample (also DecArgs.K of the launch).
-int decode_teams(int K, int64_t wfloats, int64_t n_lanes, int order, int64_t rows, int cus, size_t lds);
+// So the line is at two lanes per CU, for two teams by the waves that have pixels
+// and the depth, in either wavefront layout, where the window fits the LDS
+// left by the weights.
+struct TeamQuery {
+  int C, nb;           // the model's channels (padded) and blocks
+  int K;               // rANS streams per lane, 0 to sample (also DecArgs.K of the launch)
+  int order;
+  int64_t wfloats, n_lanes;
+  int64_t rows;        // window rows of the tallest lane
+  int step_rows;       // the most rows of a wavefront step (0: not known)
+  int cus;
+  size_t lds;
+};
+int decode_teams(const TeamQuery& q);
+// the waves of a team with pixels in a group of that many rows (team_row)
+constexpr int team_busy(int K, int rows) {
+  const int r = rows < 1 || rows > 16 ? 16 : rows;
+  return K == 8 ? ((r < 8 ? r : 8) + 1) / 2 : (r + 3) / 4;
+}
+// the rule without the window
+constexpr int team_count(int C, int nb, int K, int64_t n_lanes, int step_rows, int cus) {
+  if (n_lanes < 1 || n_lanes > 2 * (int64_t)cus) return 0;
+  if (C <= 16 && nb > 8 && K == 4) return 0;
+  if (n_lanes <= cus) return 1;
+  const bool deep = C >= 64 ? false : C >= 32 ? nb > 4 : nb > 0;
+  return deep && K != 2 && team_busy(K, step_rows) > 2 ? 0 : 2;
+}
 hipError_t launch_decode_team(int h, int C, const DecArgs& a, int teams, hipStream_t s);
 // raise the LDS limit of the team kernel for K, or of the row-stream decoder
 hipError_t prepare_team(int h, int C, int K);

@@ -770,10 +770,10 @@ static size_t team_lds(int64_t wfloats, int teams, int rows, bool serial) {
   return (size_t)(wfloats + teams * team_words(rows, serial)) * sizeof(float);
 }
 
-int decode_teams(int K, int64_t wfloats, int64_t n_lanes, int order, int64_t rows, int cus, size_t lds) {
-  if (order == 0 || n_lanes < 1 || n_lanes > 2 * (int64_t)cus || rows < 4 || rows > 4096) return 0;
-  const int teams = n_lanes > cus ? 2 : 1;
-  return team_lds(wfloats, teams, (int)rows, K > 0 && K < 8) <= lds ? teams : 0;
+int decode_teams(const TeamQuery& q) {
+  if (q.order == 0 || q.rows < 4 || q.rows > 4096) return 0;
+  const int teams = team_count(q.C, q.nb, q.K, q.n_lanes, q.step_rows, q.cus);
+  return teams && team_lds(q.wfloats, teams, (int)q.rows, q.K > 0 && q.K < 8) <= q.lds ? teams : 0;
 }
 
 template <int H_, int C_>

@@ -28,7 +28,7 @@ static int teams_;
 #define OK return hipSuccess
 namespace nx {
 bool supported(int, int) { return true; }
-int decode_teams(int, int64_t, int64_t, int order, int64_t, int, size_t) { return order == 0 ? 0 : teams_; }
+int decode_teams(const TeamQuery& q) { return q.order == 0 ? 0 : teams_; }
 hipError_t prepare_team(int, int, int K) { log_ += " set:team" + std::to_string(K); OK; }
 hipError_t prepare_rows(int, int) { log_ += " set:rows"; OK; }
 hipError_t prepare_decode(int, int, int K) { log_ += " set:wave" + std::to_string(K); OK; }
