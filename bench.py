@@ -6,8 +6,8 @@ RGB (smooth random fields, sigma 4 px, 20 step edges, +-3 integer noise),
 coded with the h=3, 64-channel, 2-block local model (random-init weights) in
 the wavefront order with independent patches of 64 columns, each patch one
 lane of 16 interleaved rANS streams (one per row of a 16-row group); the
-patch height is the shortest that keeps the batch at two lanes per SIMD (86
-rows on 256 CUs: 1,920 lanes). One timed step = one decode
+patch height is the shortest that keeps the batch at two lanes per SIMD (82
+rows on 256 CUs: 2,032 lanes). One timed step = one decode
 of the whole batch from containers already resident in HBM, by default in the
 sheared layout (ShearLoC, Sec. 3.1 and Algorithm 2); the unsheared wavefront
 decoder (Algorithm 1) is timed on the same containers as a second leg.

@@ -451,7 +451,7 @@ NXD void net_forward(const float* __restrict__ w, int nb, const float (&ctx)[con
 // tiles instead, a team's layers cost six exchanges through LDS a group, 600
 // cycles each (model B's network 7.3 thousand cycles a group so, about 6 as
 // here; one 1024 x 1024 image with a stream per row, with the link wave:
-// 34.6 -> 29.9 ms).
+// 34.6 -> 29.9 ms, 28.6 now).
 constexpr int quad_inputs(int h) { return (4 * conv_chunks(h) + 15) / 16; }
 constexpr int HB_STRIDE = 132;  // floats per pixel of a head table
 template <int A>

@@ -483,9 +483,9 @@ __global__ void __launch_bounds__(2 * TEAM_WAVES * 64) k_decode_team(DecArgs A) 
 // step of Algorithm 1 in parallel); a row's coder state stays in the registers
 // of the lanes that decode it. A band's top rows read the h rows above,
 // decoded by the band above it, possibly on another CU: each band publishes
-// how many steps it has finished (release), and its first wave waits before
-// step t until the band above has finished step t - 1 (acquire), then copies
-// those rows' pixels of that step, at most h, into the band's window. Bands
+// how many steps it has finished (release), and before step t a wave of its
+// own (link) waits until the band above has finished step t - 1 (acquire), then
+// copies those rows' pixels of that step, at most h, into the window. Bands
 // are taken from the queue in order (by the step they start at, across the
 // images of the batch), so the band above is always held by a running or
 // finished workgroup; its skew of (h + 1) ROW_BAND steps makes waits rare once
@@ -518,11 +518,12 @@ constexpr int band_rows() { return (ROW_BAND + H_ + 3) / 4 * 4; }
 // The workgroup has a fifth wave, the band's link to its neighbours: after
 // each step's barrier it stores the step's pixels, publishes the step and
 // fetches the rows above for the next, so that neither the release nor those
-// loads are on the team's path (1,100 of 16,500 cycles a step when the team's
-// first wave did it). The pixels are its stores because a release waits for
-// the stores of its own wave alone, and a barrier of the workgroup for no
-// store to memory: another wave's could still be on their way when the step
-// is published.
+// loads and stores are on the team's path (1,100 of 16,500 cycles a step when
+// the team's first wave did it). The pixels are its stores because a release
+// waits for the stores of its own wave alone, and a barrier of the workgroup
+// for no store to memory: another wave's could still be on their way when the
+// step is published. (One 1024 x 1024 image, h = 3, 64 channels, 2 blocks:
+// 29.7 -> 28.6 ms, 13.5 thousand cycles a step.)
 constexpr int ROW_BLOCK = 64 * (ROW_WAVES + 1);
 
 template <int H_, int C_>
